@@ -379,7 +379,7 @@ int fwrs_tick(const fwrs_frame* frames, int n, void* hip_stream);
  * that must not call hipMalloc: under HIP graph capture, in tight serving
  * loops, or in harnesses that forbid it).  Same arguments and results as
  * fwrs_tick, for at most 256 entries (FWRS_E_ARG beyond, before any device
- * work).  The descriptor table lives in a fixed 46 KiB array in device memory
+ * work).  The descriptor table lives in a fixed 48 KiB array in device memory
  * that the library holds for the process's lifetime -- one per GPU, shared by
  * every call on that GPU -- and is written by small kernels whose arguments
  * carry the descriptors, on hip_stream, before the batched kernel (a call of

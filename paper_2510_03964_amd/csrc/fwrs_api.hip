@@ -184,6 +184,7 @@ struct fwrs_ctx {
     uint32_t resolved_at = 0;
     bool resolved = false;
     int tile_x = kDefaultTileX, tile_y = kDefaultTileY;
+    bool tame = true;                // every frame pushed since the last clear was tame (fwrs::frame_tame)
     hipEvent_t order_ev = nullptr;   // marks this context's stream for work on other streams
     // batched ticks: the layout pass that last met this context, and its group there
     uint64_t tick_mark = 0;
@@ -217,6 +218,7 @@ int clear_store(fwrs_ctx* x)
     if (fwrs::launch_fill_u32(reinterpret_cast<uint32_t*>(x->stats), kStatBytes / 4, 0u, x->stream) != hipSuccess)
         return FWRS_E_HIP;
     x->t = 0;
+    x->tame = true;
     x->pixel_updates = 0;
     x->resolved = false;
     return FWRS_OK;
@@ -231,6 +233,21 @@ void fill_geometry(FrameDesc& d, int width, int height, int tx, int ty)
     const uint32_t tiles_y = ((uint32_t)height + (uint32_t)ty - 1) / (uint32_t)ty;
     const uint32_t tiles_per_item = (uint32_t)fwrs::kBlock / (uint32_t)(tx * ty);
     d.items = (d.tiles_x * tiles_y + tiles_per_item - 1) / tiles_per_item;
+    // tile / tiles_x for tile < 2^31 by multiplication: with l = ceil(log2 tiles_x) and
+    // m = ceil(2^(31 + l) / tiles_x) < 2^32, m tiles_x exceeds 2^(31 + l) by less than 2^l
+    d.div_m = d.div_s = 0u;
+    if (d.tiles_x > 1u) {
+        uint32_t l = 1u;
+        while (l < 31u && (1u << l) < d.tiles_x) ++l;
+        d.div_m = (uint32_t)(((1ull << (31u + l)) + d.tiles_x - 1u) / d.tiles_x);
+        d.div_s = l - 1u;
+    }
+}
+
+// Whether x is still tame after a frame at this gaze, given that it was before.
+bool tame_at(const fwrs_ctx* x, bool before, float gx, float gy)
+{
+    return before && fwrs::frame_tame(x->c, (uint32_t)x->width, (uint32_t)x->height, gx, gy);
 }
 
 bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
@@ -257,6 +274,7 @@ FrameDesc make_desc(const fwrs_ctx* x, const float* color, const uint8_t* level,
     d.stream_id = x->prm.stream_id;
     d.bias = x->prm.bias_mode;
     d.k = (uint32_t)x->k;
+    d.tame = tame_at(x, x->tame, gx, gy) ? 1u : 0u;
     fill_geometry(d, x->width, x->height, tx, ty);
     return d;
 }
@@ -284,12 +302,13 @@ bool plane_after(const fwrs_ctx* x, int op)
     return op == fwrs::kOpCached || op == fwrs::kOpFill || (op == fwrs::kOpGroup && x->res);
 }
 
-// After a successful launch of `op` on x: the frame count, the record of the
-// last resolve target and the validity of the resolve plane.  (A group of
-// frames advances x once per frame, in order.)
-void advance(fwrs_ctx* x, int op, const float* out)
+// After a successful launch of `op` on x at a gaze: the frame count, the record
+// of the last resolve target and the validity of the resolve plane.  (A group
+// of frames advances x once per frame, in order.)
+void advance(fwrs_ctx* x, int op, const float* out, float gx, float gy)
 {
     if (op != fwrs::kOpResolve) {
+        x->tame = tame_at(x, x->tame, gx, gy);
         x->t += 1u;
         x->pixel_updates += (uint64_t)x->width * (uint64_t)x->height;
         x->res_valid = plane_after(x, op);
@@ -310,7 +329,7 @@ int run_frame(fwrs_ctx* x, const float* color, const uint8_t* level, float gx, f
     if (op == fwrs::kOpFused) op = fused_op(x);
     FrameDesc d = make_desc(x, color, level, gx, gy, out, x->tile_x, x->tile_y);
     if (fwrs::launch_frame(d, op, x->stream) != hipSuccess) return FWRS_E_HIP;
-    advance(x, op, out);
+    advance(x, op, out, gx, gy);
     return FWRS_OK;
 }
 
@@ -513,6 +532,7 @@ int fwrs_push_frame_reproject(fwrs_ctx* x, const float* color, const uint8_t* le
     x->wsum = x->bank_wsum[dst];
     x->rec = x->bank_rec[dst];
     x->idx = x->bank_idx[dst];
+    x->tame = r.f.tame != 0u;
     x->t += 1u;
     x->pixel_updates += (uint64_t)x->width * (uint64_t)x->height;
     x->resolved = false;
@@ -722,19 +742,21 @@ int check_tick(const fwrs_frame* frames, int n, int max_frames, int device)
 }
 
 // Scratch of the tick layout for up to m entries: kTickWorkInts * m ints.
-constexpr size_t kTickWorkInts = 6;
+constexpr size_t kTickWorkInts = 7;
 struct TickWork {
     int* group;     // [entry] its context's group
     int* count;     // [group] entries
     int* pos;       // [group] entries laid out so far
     int* slot;      // [group] the leader's table index
     int* base;      // [group] table index of the group's second frame
-    int* plane;     // [group] whether the resolve plane is whole before the entry being laid out
+    int* plane;     // [group] before the entry being laid out: 1 the resolve plane is whole, 2 the context is tame
+    int* tame;      // [group] its context is tame after all its entries
     TickWork(int* w, size_t m)
-        : group(w), count(w + m), pos(w + 2 * m), slot(w + 3 * m), base(w + 4 * m), plane(w + 5 * m) {}
+        : group(w), count(w + m), pos(w + 2 * m), slot(w + 3 * m), base(w + 4 * m), plane(w + 5 * m),
+          tame(w + 6 * m) {}
 };
 
-// Whether pixel_group runs x's groups: compile-time slot counts and one w_sum per pixel.
+// Whether pixel_group runs x's groups of tame frames: compile-time slot counts and one w_sum per pixel.
 bool group_kernel(const fwrs_ctx* x)
 {
     return (x->k == 1 || x->k == 2 || x->k == 4 || x->k == 8) && !fwrs::per_slot_mode(x->prm.bias_mode);
@@ -763,9 +785,11 @@ int layout_tick(const fwrs_frame* frames, int n, bool reverse, TileFn tile, Tick
             x->tick_group = groups;
             w.count[groups] = 0;
             w.pos[groups] = 0;
-            w.plane[groups] = x->res_valid ? 1 : 0;
+            w.plane[groups] = (x->res_valid ? 1 : 0) | (x->tame ? 2 : 0);
+            w.tame[groups] = x->tame ? 1 : 0;
             ++groups;
         }
+        w.tame[x->tick_group] = tame_at(x, w.tame[x->tick_group] != 0, frames[i].gaze_x, frames[i].gaze_y) ? 1 : 0;
         w.group[i] = x->tick_group;
         w.count[x->tick_group] += 1;
         if ((uint64_t)x->t + (uint64_t)w.count[x->tick_group] > 0xFFFFFFFFull) return FWRS_E_STATE;
@@ -788,9 +812,11 @@ int layout_tick(const fwrs_frame* frames, int n, bool reverse, TileFn tile, Tick
         FrameDesc& d = descs[at == 0 ? w.slot[g] : w.base[g] + at - 1];
         d = make_desc(x, f.color, f.level_map, f.gaze_x, f.gaze_y, f.out, tx, ty);
         d.t = x->t + (uint32_t)at;
-        const bool plane = w.plane[g] != 0;
-        const int op = nf > 1 && group_kernel(x) ? fwrs::kOpGroup : fused_op_at(x, d.t, plane);
-        w.plane[g] = plane_after(x, op) ? 1 : 0;
+        const bool plane = (w.plane[g] & 1) != 0;
+        const bool tame = tame_at(x, (w.plane[g] & 2) != 0, f.gaze_x, f.gaze_y);
+        const int op = nf > 1 && w.tame[g] != 0 && group_kernel(x) ? fwrs::kOpGroup : fused_op_at(x, d.t, plane);
+        w.plane[g] = (plane_after(x, op) ? 1 : 0) | (tame ? 2 : 0);
+        d.tame = tame ? 1u : 0u;
         if (nf > 1 && kind != fwrs::kTickGroups8)
             kind = op == fwrs::kOpGroup && x->k == 8 ? fwrs::kTickGroups8 : fwrs::kTickGroups;
         ops[i] = op;
@@ -1000,7 +1026,7 @@ int engine_tick(fwrs_engine* e, const fwrs_frame* frames, int n, hipStream_t str
     }
     if (!in_args) sl.pending = true;
     e->ticks += 1u;
-    for (int i = 0; i < n; ++i) advance(frames[i].ctx, e->ops[i], frames[i].out);
+    for (int i = 0; i < n; ++i) advance(frames[i].ctx, e->ops[i], frames[i].out, frames[i].gaze_x, frames[i].gaze_y);
     // ... and its later work (and fwrs_destroy) waits for this tick
     if (foreign) {
         if (!e->done_ev && hipEventCreateWithFlags(&e->done_ev, hipEventDisableTiming) != hipSuccess) {
@@ -1190,7 +1216,7 @@ int fwrs_tick_noalloc(const fwrs_frame* frames, int n, void* hip_stream)
             return FWRS_E_HIP;
         }
         g_scratch_ticks[dev] += 1u;
-        for (int i = 0; i < n; ++i) advance(frames[i].ctx, ops[i], frames[i].out);
+        for (int i = 0; i < n; ++i) advance(frames[i].ctx, ops[i], frames[i].out, frames[i].gaze_x, frames[i].gaze_y);
         return FWRS_OK;
     }
     FrameDesc descs[kStaticTickFrames];
@@ -1212,7 +1238,7 @@ int fwrs_tick_noalloc(const fwrs_frame* frames, int n, void* hip_stream)
         return FWRS_E_HIP;
     }
     g_scratch_ticks[dev] += 1u;
-    for (int i = 0; i < n; ++i) advance(frames[i].ctx, ops[i], frames[i].out);
+    for (int i = 0; i < n; ++i) advance(frames[i].ctx, ops[i], frames[i].out, frames[i].gaze_x, frames[i].gaze_y);
     return FWRS_OK;
 }
 
@@ -1361,7 +1387,7 @@ int fwrs_push_frame_foveated(fwrs_ctx* x, fwrs_foveator* f, const float* full, f
     fd.f = make_desc(x, nullptr, nullptr, gaze_x, gaze_y, out, x->tile_x, x->tile_y);
     const int op = out ? fused_op(x) : fwrs::kOpPush;
     if (fwrs::launch_foveated(fd, op, x->stream) != hipSuccess) return FWRS_E_HIP;
-    advance(x, op, out);
+    advance(x, op, out, gaze_x, gaze_y);
     if (order_after(f->stream, x->stream, x->order_ev) != hipSuccess) return FWRS_E_HIP;
     return FWRS_OK;
 }

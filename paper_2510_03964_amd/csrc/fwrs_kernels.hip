@@ -131,7 +131,7 @@ __device__ __forceinline__ Words<K> philox_words(const FrameDesc& d, uint32_t p)
     Words<K> out;
 #pragma unroll
     for (int b = 0; b < (K + 3) / 4; ++b) {
-        const uint4 r = philox4x32_10(p, d.t, (uint32_t)b, 0u, d.seed, d.stream_id);
+        const uint4 r = philox4x32_10(p, d.t, (uint32_t)b, d.seed, d.stream_id);
         out.w[4 * b + 0] = r.x;
         out.w[4 * b + 1] = r.y;
         out.w[4 * b + 2] = r.z;
@@ -146,22 +146,23 @@ __device__ __forceinline__ uint32_t decide_words(const Words<K>& words, float W1
     uint32_t mask = 0u;
 #pragma unroll
     for (int j = 0; j < K; ++j)
-        if (unit_variate(words.w[j]) * s > W1b) mask |= 1u << j;
+        if (takes<true>(words.w[j], s, W1b)) mask |= 1u << j;
     return mask;
 }
 
 // Run-time slot count: blocks drawn as needed.
+template <bool TAME>
 __device__ __forceinline__ uint32_t decide_any(const FrameDesc& d, uint32_t p, float W1b, float s)
 {
     const int kk = (int)d.k;
     uint32_t mask = 0u;
     for (int b = 0; 4 * b < kk; ++b) {
-        const uint4 r = philox4x32_10(p, d.t, (uint32_t)b, 0u, d.seed, d.stream_id);
+        const uint4 r = philox4x32_10(p, d.t, (uint32_t)b, d.seed, d.stream_id);
         const uint32_t words[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int j = 4 * b + q;
-            if (j < kk && unit_variate(words[q]) * s > W1b) mask |= 1u << j;
+            if (j < kk && takes<TAME>(words[q], s, W1b)) mask |= 1u << j;
         }
     }
     return mask;
@@ -174,9 +175,22 @@ __device__ __forceinline__ uint32_t decide_any(const FrameDesc& d, uint32_t p, f
 #define FWRS_RES_EARLY 1
 #endif
 
+// Slot-count argument of the per-pixel code: a count the code is compiled for
+// (its record in registers), 0 for any count (streamed slot by slot), or kWild:
+// any count with the general division, root and variate test, for the frames of
+// a context that is not tame (frame_tame).
+constexpr int kWild = -1;
+
 // The resolve of a record held in registers: sum_j w_j col_j / sum_j w_j, the
 // sums taken in slot order; 0 for a record with no weight (only the empty
 // reservoir: every kept weight is > 0).
+template <bool TAME>
+__device__ __forceinline__ float resolve_scale(float S)
+{
+    const float rs = TAME ? rcp_rn(S) : 1.0f / S;
+    return S > 0.0f ? rs : 0.0f;
+}
+
 template <int R>
 __device__ __forceinline__ void resolve_slots(const float4 (&r)[R], float& q0, float& q1, float& q2)
 {
@@ -188,7 +202,7 @@ __device__ __forceinline__ void resolve_slots(const float4 (&r)[R], float& q0, f
         a1 = a1 + r[j].x * r[j].z;
         a2 = a2 + r[j].x * r[j].w;
     }
-    const float rs = S > 0.0f ? 1.0f / S : 0.0f;
+    const float rs = resolve_scale<true>(S);
     q0 = a0 * rs;
     q1 = a1 * rs;
     q2 = a2 * rs;
@@ -199,10 +213,12 @@ __device__ __forceinline__ void resolve_slots(const float4 (&r)[R], float& q0, f
 // (any slot count up to kMaxK) streams the record one slot at a time.
 // Returns the number of slots replaced plus 2^16 if there was any.
 // ---------------------------------------------------------------------------
-template <int K, int OP, bool FOV = false>
+template <int SLOTS, int OP, bool FOV = false>
 __device__ __forceinline__ uint32_t pixel(const FrameDesc& d, uint32_t x, uint32_t y, const FovSrc* fs = nullptr)
 {
     const uint32_t p = y * d.width + x;
+    constexpr bool kTame = SLOTS != kWild;
+    constexpr int K = SLOTS > 0 ? SLOTS : 0;
     const int kk = K ? K : (int)d.k;
     constexpr int R = K ? K : 1;
     constexpr bool kUpdates = OP != kResolve;
@@ -250,7 +266,7 @@ __device__ __forceinline__ uint32_t pixel(const FrameDesc& d, uint32_t x, uint32
         if (K) words = philox_words<R>(d, p);
         const float dx = ((float)x + 0.5f) - d.gx;
         const float dy = ((float)y + 0.5f) - d.gy;
-        outside = weight_outside(d.c, dx * dx + dy * dy, e);
+        outside = weight_outside<kTame>(d.c, dx * dx + dy * dy, e);
     }
 
     // 3. weight (Eq. 4), bias (Eq. 6) and the Alg. 2 decision per slot
@@ -258,9 +274,9 @@ __device__ __forceinline__ uint32_t pixel(const FrameDesc& d, uint32_t x, uint32
     float w = 0.f, s = 0.f;
     if (kUpdates) {
         w = select_eq4(d.c, outside, e, lv);
-        const float W1b = bias_shared(W1, w, d.bias, d.c.decay);
+        const float W1b = bias_shared<kTame>(W1, w, d.bias, d.c.decay);
         s = W1b + w;
-        tk = K ? decide_words<R>(words, W1b, s) : decide_any(d, p, W1b, s);
+        tk = K ? decide_words<R>(words, W1b, s) : decide_any<kTame>(d, p, W1b, s);
     }
 
     // 4. the loads the decision calls for, all issued before any is waited for:
@@ -336,7 +352,7 @@ __device__ __forceinline__ uint32_t pixel(const FrameDesc& d, uint32_t x, uint32
                     a2 = a2 + v.x * v.w;
                 }
                 // S == 0 only before the first frame (every kept weight is > 0): output 0.
-                const float rs = S > 0.0f ? 1.0f / S : 0.0f;
+                const float rs = resolve_scale<kTame>(S);
                 q0 = a0 * rs;
                 q1 = a1 * rs;
                 q2 = a2 * rs;
@@ -466,9 +482,9 @@ __device__ __forceinline__ void pixel_group(const FrameDesc& d0, const FrameDesc
         const float dx = ((float)x + 0.5f) - d.gx;
         const float dy = ((float)y + 0.5f) - d.gy;
         float e = 0.f;
-        const float outside = weight_outside(d.c, dx * dx + dy * dy, e);
+        const float outside = weight_outside<true>(d.c, dx * dx + dy * dy, e);
         const float w = select_eq4(d.c, outside, e, lv);
-        const float W1b = bias_shared(W1, w, d.bias, d.c.decay);
+        const float W1b = bias_shared<true>(W1, w, d.bias, d.c.decay);
         const float s = W1b + w;
         const uint32_t tk = decide_words<K>(philox_words<K>(d, p), W1b, s);
         W1 = s;
@@ -515,11 +531,13 @@ __device__ __forceinline__ void pixel_group(const FrameDesc& d0, const FrameDesc
 // Needs the new colour for every pixel and every slot's record, so the records
 // are read by every op that updates.  Same store layout otherwise.
 // ---------------------------------------------------------------------------
-template <int K, int OP, bool FOV = false>
+template <int SLOTS, int OP, bool FOV = false>
 __device__ __forceinline__ uint32_t pixel_per_slot(const FrameDesc& d, uint32_t x, uint32_t y,
                                                    const FovSrc* fs = nullptr)
 {
     const uint32_t p = y * d.width + x;
+    constexpr bool kTame = SLOTS != kWild;
+    constexpr int K = SLOTS > 0 ? SLOTS : 0;
     const int kk = K ? K : (int)d.k;
     constexpr int R = K ? K : 1;
     constexpr bool kUpdates = OP == kPush || OP == kFused || OP == kIncremental;
@@ -565,7 +583,7 @@ __device__ __forceinline__ uint32_t pixel_per_slot(const FrameDesc& d, uint32_t 
     }
     const float dx = ((float)x + 0.5f) - d.gx;
     const float dy = ((float)y + 0.5f) - d.gy;
-    const float w = weight_eq4(d.c, dx * dx + dy * dy, lv);
+    const float w = weight_eq4<kTame>(d.c, dx * dx + dy * dy, lv);
     const bool aes = d.bias == kAes;
     // Eq. 7: a slot whose sample has the new pixel's colour has |dL| = 0 exactly
     // (same_colour), so its Lab and CIE94 are not evaluated, nor the new
@@ -588,7 +606,7 @@ __device__ __forceinline__ uint32_t pixel_per_slot(const FrameDesc& d, uint32_t 
     for (int j = 0; j < kk; ++j) {
         float4 v = K ? r[K ? j : 0] : ld4<kNtRecLd>(rec + j);
         const float W1 = K ? W[K ? j : 0] : ld<kNtWsumLd>(wslot + j);
-        if ((j & 3) == 0) words = philox4x32_10(p, d.t, (uint32_t)(j >> 2), 0u, d.seed, d.stream_id);
+        if ((j & 3) == 0) words = philox4x32_10(p, d.t, (uint32_t)(j >> 2), d.seed, d.stream_id);
         const uint32_t word = (j & 3) == 0 ? words.x : (j & 3) == 1 ? words.y : (j & 3) == 2 ? words.z : words.w;
         bool take;
         float s;
@@ -602,9 +620,9 @@ __device__ __forceinline__ uint32_t pixel_per_slot(const FrameDesc& d, uint32_t 
             const bool same_j = K ? ((same >> j) & 1u) != 0u : bounded && same_colour(v, c0, c1, c2);
             float dl = 0.0f;
             if (!same_j) dl = delta_l(v.y, v.z, v.w, lab_new);
-            const float W1b = bias_eq7(W1, w, dl);
+            const float W1b = bias_eq7<kTame>(W1, w, dl);
             s = W1b + w;
-            take = unit_variate(word) * s > W1b;
+            take = takes<kTame>(word, s, W1b);
         }
         if (take) {
             tk |= 1u << j;
@@ -631,7 +649,7 @@ __device__ __forceinline__ uint32_t pixel_per_slot(const FrameDesc& d, uint32_t 
         }
     }
     if (kResolves && (OP != kIncremental || tk)) {
-        const float rs = S > 0.0f ? 1.0f / S : 0.0f;
+        const float rs = resolve_scale<kTame>(S);
         float* o = d.out + 3 * (size_t)p;
         st<kNtOut>(o + 0, a0 * rs);
         st<kNtOut>(o + 1, a1 * rs);
@@ -656,7 +674,7 @@ __device__ __forceinline__ bool item_pixel_of(const FrameDesc& d, uint32_t item,
     const uint32_t tiles_per_item_log2 = 8u - tlog;
     const uint32_t tile = (item << tiles_per_item_log2) + (wave >> waves_per_tile_log2);
     const uint32_t local = ((wave & ((1u << waves_per_tile_log2) - 1u)) << 6) | lane;
-    const uint32_t ty = tile / d.tiles_x;
+    const uint32_t ty = d.div_m ? __umulhi(tile, d.div_m) >> d.div_s : tile;
     const uint32_t tx = tile - ty * d.tiles_x;
     x = (tx << d.tile_x_log2) + (local & ((1u << d.tile_x_log2) - 1u));
     y = (ty << d.tile_y_log2) + (local >> d.tile_x_log2);
@@ -679,35 +697,45 @@ __device__ __forceinline__ uint32_t process_item(const FrameDesc& d, uint32_t it
     return pixel<K, OP, FOV>(d, x, y, fs);
 }
 
+// Sum of v over the wave, in every lane: five row-wise steps by data-parallel
+// moves (no LDS traffic) and the last lane's total as a scalar.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
+{
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);    // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);    // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);    // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);    // row_shr:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);   // row_bcast:15, rows 1 and 3
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);   // row_bcast:31, rows 2 and 3
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// The wave's counts go to a triple chosen by the wave's id, lane c adding
+// counter c: one atomic instruction per wave.
+__device__ __forceinline__ void add_counts(unsigned long long* stats, uint32_t slots, uint32_t changed,
+                                           uint32_t flushed)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    if (lane < (flushed ? 3u : 2u)) {
+        const uint32_t slot = (blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) & (kStatSlots - 1);
+        atomicAdd(stats + 3 * slot + lane, (unsigned long long)(lane == 0u ? slots : lane == 1u ? changed : flushed));
+    }
+}
+
 // add_stats for counts beyond its packed fields' range (a group of frames):
 // replaced slots and changed pixel-frames as separate wave sums.
 __device__ __forceinline__ void add_stats_wide(unsigned long long* stats, uint32_t slots, uint32_t changed)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        slots += __shfl_xor(slots, off);
-        changed += __shfl_xor(changed, off);
-    }
-    if ((threadIdx.x & 63u) == 0u && changed) {
-        const uint32_t slot = (blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) & (kStatSlots - 1);
-        atomicAdd(stats + 3 * slot, (unsigned long long)slots);
-        atomicAdd(stats + 3 * slot + 1, (unsigned long long)changed);
-    }
+    changed = wave_sum(changed);
+    if (changed) add_counts(stats, wave_sum(slots), changed, 0u);
 }
 
 __device__ __forceinline__ void add_stats(unsigned long long* stats, uint32_t v)
 {
-    // v = replaced slots + 2^16 * (pixel changed) + 2^24 * (pixel flushed).  Wave sum (at
-    // most 1024 slots and 64 pixels per field), then one 64-bit atomic per non-zero counter
-    // and wave on a triple chosen by the wave's id.
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    if ((threadIdx.x & 63u) == 0u && v) {
-        const uint32_t slot = (blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) & (kStatSlots - 1);
-        atomicAdd(stats + 3 * slot, (unsigned long long)(v & 0xFFFFu));
-        atomicAdd(stats + 3 * slot + 1, (unsigned long long)((v >> 16) & 0xFFu));
-        if (v >> 24) atomicAdd(stats + 3 * slot + 2, (unsigned long long)(v >> 24));
-    }
+    // v = replaced slots + 2^16 * (pixel changed) + 2^24 * (pixel flushed); the wave sum
+    // has at most 1024 slots and 64 pixels per field
+    v = wave_sum(v);
+    if (v) add_counts(stats, v & 0xFFFFu, (v >> 16) & 0xFFu, v >> 24);
 }
 
 // Work items are visited in reverse order on odd frames, so each frame starts
@@ -758,10 +786,12 @@ __device__ __forceinline__ uint32_t process_wave(const FrameDesc& d, uint32_t it
 
 __device__ __forceinline__ uint32_t tick_item(const FrameDesc& d, uint32_t local, uint32_t wave)
 {
-    if (per_slot_mode(d.bias)) return process_wave<0, kFused, true>(d, local, wave);
+    if (per_slot_mode(d.bias))
+        return d.tame ? process_wave<0, kFused, true>(d, local, wave) : process_wave<kWild, kFused, true>(d, local, wave);
 #define FWRS_TICK_OPS(KK)                                                                  \
     return d.op == kCached ? process_wave<KK, kCached>(d, local, wave)                     \
          : d.op == kFill ? process_wave<KK, kFill>(d, local, wave) : process_wave<KK, kFused>(d, local, wave)
+    if (!d.tame) FWRS_TICK_OPS(kWild);
     switch (d.k) {
         case 1: FWRS_TICK_OPS(1);
         case 2: FWRS_TICK_OPS(2);
@@ -871,11 +901,13 @@ __global__ __launch_bounds__(64) void tick_fill_kernel(uint32_t* __restrict__ ta
 // written densely to this frame's bank, and the resolve.  A gather from the
 // previous bank, so the banks alternate; every slot is rewritten.
 // ---------------------------------------------------------------------------
-template <int K, bool PER_SLOT>
+template <int SLOTS, bool PER_SLOT>
 __device__ __forceinline__ uint32_t pixel_reproject(const ReprojDesc& r, uint32_t x, uint32_t y)
 {
     const FrameDesc& d = r.f;
     const uint32_t p = y * d.width + x;
+    constexpr bool kTame = SLOTS != kWild;
+    constexpr int K = SLOTS > 0 ? SLOTS : 0;
     const int kk = K ? K : (int)d.k;
     constexpr int R = K ? K : 1;
 
@@ -935,7 +967,7 @@ __device__ __forceinline__ uint32_t pixel_reproject(const ReprojDesc& r, uint32_
     const float c2 = ld<kNtColor>(color + 2);
     const float dx = ((float)x + 0.5f) - d.gx;
     const float dy = ((float)y + 0.5f) - d.gy;
-    const float w = weight_eq4(d.c, dx * dx + dy * dy, lv);
+    const float w = weight_eq4<kTame>(d.c, dx * dx + dy * dy, lv);
     const float4 fresh = make_float4(w, c0, c1, c2);
     // Eq. 7: a slot whose sample has the new pixel's colour has |dL| = 0 exactly
     // (same_colour); neither Lab is evaluated for it
@@ -948,7 +980,7 @@ __device__ __forceinline__ uint32_t pixel_reproject(const ReprojDesc& r, uint32_
     }
     float3 lab_new = make_float3(0.f, 0.f, 0.f);
     if (PER_SLOT && !aes && (!K || same != (1u << R) - 1u)) lab_new = rgb_to_lab(c0, c1, c2);
-    const float W1b = PER_SLOT ? 0.f : bias_shared(W1, w, d.bias, d.c.decay);
+    const float W1b = PER_SLOT ? 0.f : bias_shared<kTame>(W1, w, d.bias, d.c.decay);
     const float s = W1b + w;
 
     // 4. Alg. 2 per slot, dense stores to this frame's bank, resolve sums
@@ -976,7 +1008,7 @@ __device__ __forceinline__ uint32_t pixel_reproject(const ReprojDesc& r, uint32_
                 Wj = keep ? ws : empty_slot;
             }
         }
-        if ((j & 3) == 0) words = philox4x32_10(p, d.t, (uint32_t)(j >> 2), 0u, d.seed, d.stream_id);
+        if ((j & 3) == 0) words = philox4x32_10(p, d.t, (uint32_t)(j >> 2), d.seed, d.stream_id);
         const uint32_t word = (j & 3) == 0 ? words.x : (j & 3) == 1 ? words.y : (j & 3) == 2 ? words.z : words.w;
         float W1j = W1b, sj = s;
         bool take;
@@ -989,11 +1021,11 @@ __device__ __forceinline__ uint32_t pixel_reproject(const ReprojDesc& r, uint32_
                 const bool same_j = K ? ((same >> j) & 1u) != 0u : bounded && same_colour(v, c0, c1, c2);
                 float dl = 0.0f;
                 if (!same_j) dl = delta_l(v.y, v.z, v.w, lab_new);
-                W1j = bias_eq7(Wj, w, dl);
+                W1j = bias_eq7<kTame>(Wj, w, dl);
                 sj = W1j + w;
                 st<kNtWsumSt>(d.wsum + (size_t)p * (size_t)kk + j, sj);
             }
-            take = unit_variate(word) * sj > W1j;
+            take = takes<kTame>(word, sj, W1j);
         }
         if (take) {
             tk |= 1u << j;
@@ -1011,7 +1043,7 @@ __device__ __forceinline__ uint32_t pixel_reproject(const ReprojDesc& r, uint32_
     st<kNtWsumSt>(r.cnt + p, m + 1u);
     st<kNtWsumSt>(r.depth_out + p, dc);
     if (d.out) {
-        const float rs = S > 0.0f ? 1.0f / S : 0.0f;
+        const float rs = resolve_scale<kTame>(S);
         float* o = d.out + 3 * (size_t)p;
         st<kNtOut>(o + 0, a0 * rs);
         st<kNtOut>(o + 1, a1 * rs);
@@ -1024,22 +1056,10 @@ template <int K, bool PER_SLOT>
 __global__ __launch_bounds__(kBlock) void reproject_kernel(ReprojDesc r)
 {
     const FrameDesc& d = r.f;
-    const uint32_t tid = threadIdx.x;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t lane = tid & 63u;
-    const uint32_t tlog = d.tile_x_log2 + d.tile_y_log2;
-    const uint32_t waves_per_tile_log2 = tlog - 6u;
-    const uint32_t tiles_per_item_log2 = 8u - tlog;
     // forward order every frame: this dense pass (221 B per pixel) gains nothing
     // from the Infinity Cache and streams slightly slower backwards
-    const uint32_t tile = (blockIdx.x << tiles_per_item_log2) + (wave >> waves_per_tile_log2);
-    const uint32_t local = ((wave & ((1u << waves_per_tile_log2) - 1u)) << 6) | lane;
-    const uint32_t ty = tile / d.tiles_x;
-    const uint32_t tx = tile - ty * d.tiles_x;
-    const uint32_t x = (tx << d.tile_x_log2) + (local & ((1u << d.tile_x_log2) - 1u));
-    const uint32_t y = (ty << d.tile_y_log2) + (local >> d.tile_x_log2);
-    uint32_t n = 0u;
-    if (y < d.height && x < d.width) n = pixel_reproject<K, PER_SLOT>(r, x, y);
+    uint32_t x, y, n = 0u;
+    if (item_pixel(d, blockIdx.x, x, y)) n = pixel_reproject<K, PER_SLOT>(r, x, y);
     if (d.stats) add_stats(d.stats, n);
 }
 
@@ -1339,14 +1359,19 @@ __global__ void fill_u32_kernel(uint32_t* __restrict__ p, size_t n, uint32_t v)
 // ---------------------------------------------------------------------------
 // Host-side launchers.
 // ---------------------------------------------------------------------------
+// The per-pixel code's slot-count argument for a frame.
+static int slots_arg(const FrameDesc& d) { return d.tame ? (int)d.k : kWild; }
+
 template <int OP>
 static hipError_t launch_frame_op(const FrameDesc& d, hipStream_t stream)
 {
     const dim3 grid(d.items), block(kBlock);
+    const int slots = slots_arg(d);
     // the per-slot modes keep no resolve plane: they run kPush, kFused or kIncremental
     if constexpr (OP == kPush || OP == kFused || OP == kIncremental) {
         if (per_slot_mode(d.bias)) {
-            switch (d.k) {
+            switch (slots) {
+                case kWild: hipLaunchKernelGGL((frame_kernel<kWild, OP, true>), grid, block, 0, stream, d); break;
                 case 4: hipLaunchKernelGGL((frame_kernel<4, OP, true>), grid, block, 0, stream, d); break;
                 case 8: hipLaunchKernelGGL((frame_kernel<8, OP, true>), grid, block, 0, stream, d); break;
                 default: hipLaunchKernelGGL((frame_kernel<0, OP, true>), grid, block, 0, stream, d); break;
@@ -1354,7 +1379,8 @@ static hipError_t launch_frame_op(const FrameDesc& d, hipStream_t stream)
             return hipGetLastError();
         }
     }
-    switch (d.k) {
+    switch (slots) {
+        case kWild: hipLaunchKernelGGL((frame_kernel<kWild, OP>), grid, block, 0, stream, d); break;
         case 1: hipLaunchKernelGGL((frame_kernel<1, OP>), grid, block, 0, stream, d); break;
         case 2: hipLaunchKernelGGL((frame_kernel<2, OP>), grid, block, 0, stream, d); break;
         case 4: hipLaunchKernelGGL((frame_kernel<4, OP>), grid, block, 0, stream, d); break;
@@ -1401,7 +1427,11 @@ hipError_t launch_reproject(const ReprojDesc& r, hipStream_t stream)
 {
     const dim3 grid(r.f.items), block(kBlock);
     const bool eq7 = per_slot_mode(r.f.bias);
-    switch (r.f.k) {
+    switch (slots_arg(r.f)) {
+        case kWild:
+            if (eq7) hipLaunchKernelGGL((reproject_kernel<kWild, true>), grid, block, 0, stream, r);
+            else hipLaunchKernelGGL((reproject_kernel<kWild, false>), grid, block, 0, stream, r);
+            break;
         case 4:
             if (eq7) hipLaunchKernelGGL((reproject_kernel<4, true>), grid, block, 0, stream, r);
             else hipLaunchKernelGGL((reproject_kernel<4, false>), grid, block, 0, stream, r);
@@ -1485,7 +1515,10 @@ hipError_t launch_foveated(const FovDesc& fd, int op, hipStream_t stream)
     } while (0)
     if (ps) {
         const bool push = op == kPush;
-        if (fd.f.k == 4) {
+        if (!fd.f.tame) {
+            if (push) FWRS_FOV_LAUNCH(kWild, true, kPush);
+            else FWRS_FOV_LAUNCH(kWild, true, kFused);
+        } else if (fd.f.k == 4) {
             if (push) FWRS_FOV_LAUNCH(4, true, kPush);
             else FWRS_FOV_LAUNCH(4, true, kFused);
         } else {
@@ -1493,7 +1526,8 @@ hipError_t launch_foveated(const FovDesc& fd, int op, hipStream_t stream)
             else FWRS_FOV_LAUNCH(0, true, kFused);
         }
     } else {
-        switch (fd.f.k) {
+        switch (slots_arg(fd.f)) {
+            case kWild: FWRS_FOV_OPS(kWild); break;
             case 4: FWRS_FOV_OPS(4); break;
             case 8: FWRS_FOV_OPS(8); break;
             default: FWRS_FOV_OPS(0); break;
