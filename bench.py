@@ -43,9 +43,9 @@ COUNTERS = os.path.join(ROOT, "profiles", "fused_k4_4k_counters.json")
 INC_COUNTERS = os.path.join(ROOT, "profiles", "incremental_k4_4k_counters.json")
 EQ7_COUNTERS = os.path.join(ROOT, "profiles", "eq7_k4_4k_counters.json")
 VALU_COUNTERS = os.path.join(ROOT, "profiles", "fused_valu_4k_counters.json")
-KERNEL_PLAIN = "void fwrs::frame_kernel<4, 3, false>(fwrs::FrameDesc)"
-KERNEL_FILL = "void fwrs::frame_kernel<4, 9, false>(fwrs::FrameDesc)"
-KERNEL_CACHED = "void fwrs::frame_kernel<4, 7, false>(fwrs::FrameDesc)"
+KERNEL_PLAIN = "void fwrs::frame_kernel<4, 3, false, 1>(fwrs::FrameDesc)"
+KERNEL_FILL = "void fwrs::frame_kernel<4, 9, false, 1>(fwrs::FrameDesc)"
+KERNEL_CACHED = "void fwrs::frame_kernel<4, 7, false, 1>(fwrs::FrameDesc)"
 #: VALU issue peak of the MI355X for non-packed instructions, in lane-operations per second: one wave64
 #: instruction per compute unit and clock, 256 CUs x 64 lanes x 2.4 GHz (profiles/valu_issue_rate.md measures
 #: non-packed fp32 fma / mul / add at 0.92-0.98 of it; the published 157.3 TFLOP/s fp32 vector rate counts packed
@@ -742,7 +742,7 @@ def main() -> int:
                        "roofline": {"bound": "hbm", "achieved": i_ach, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                                     "frac": i_ach / HBM_PEAK_GBPS,
                                     "traffic": traffic_from_counters(
-                                        "void fwrs::frame_kernel<4, 5, false>(fwrs::FrameDesc)", spec.pixels,
+                                        "void fwrs::frame_kernel<4, 5, false, 2>(fwrs::FrameDesc)", spec.pixels,
                                         {"steps": K, "frames_per_step": fps, "frames": n_frames}, INC_COUNTERS),
                                     "kernel_ms_avg": i_kern,
                                     "bytes_per_pixel_update": i_B, "slot_takes_per_pixel_update": i_rbar,
@@ -766,7 +766,7 @@ def main() -> int:
         f_B = bytes_per_update_eq7(spec.k, f_rbar)
         f_kern = float(f_per.mean())
         f_ach = spec.pixels * f_B / (f_kern / 1e3) / 1e9
-        e7_kernel = "void fwrs::frame_kernel<4, 3, true>(fwrs::FrameDesc)"
+        e7_kernel = "void fwrs::frame_kernel<4, 3, true, 1>(fwrs::FrameDesc)"
         vpp = valu_per_pixel(e7_kernel)
         alu = None
         if vpp is not None:
@@ -776,7 +776,7 @@ def main() -> int:
                    "wave_insts_per_cu_clock": a_t * 1e12 / 64.0 / 256.0 / 2.4e9,
                    "note": "all VALU instructions (SQ_INSTS_VALU) against one non-packed wave64 instruction per CU "
                            "and clock",
-                   "kernel": "fwrs::frame_kernel<4, 3, true> (Eq. 7)"}
+                   "kernel": "fwrs::frame_kernel<4, 3, true, 1> (Eq. 7)"}
         eq7 = {"entry": "fwrs_push_frame_resolve (FWRS_BIAS_FULL)", "frames": n_frames,
                "ms_per_frame": f_ms / n_frames,
                "value": spec.pixels * n_frames / (f_ms / 1e3) / 1e9, "unit": "Gpixel-updates/s",

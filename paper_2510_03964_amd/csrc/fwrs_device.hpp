@@ -413,6 +413,30 @@ __device__ __forceinline__ float3 fov_colour(const FovSrc& s, uint32_t x, uint32
     return level == 1u ? bilinear(s.l1, s.w1, s.h1, x, y, 0.5f) : bilinear(s.l2, s.w2, s.h2, x, y, 0.25f);
 }
 
+// One channel of fov_colour.
+__device__ __forceinline__ float fov_channel(const FovSrc& s, uint32_t x, uint32_t y, uint32_t p, uint32_t level,
+                                             uint32_t ch)
+{
+    if (level == 0u || s.mode == kFovGauss) return (level == 0u ? s.full : s.l1)[3 * (size_t)p + ch];
+    const bool one = level == 1u;
+    const float* lv = one ? s.l1 : s.l2;
+    const uint32_t w = one ? s.w1 : s.w2, h = one ? s.h1 : s.h2;
+    const float inv_scale = one ? 0.5f : 0.25f;
+    const float u = ((float)x + 0.5f) * inv_scale - 0.5f;
+    const float v = ((float)y + 0.5f) * inv_scale - 0.5f;
+    const float fu = floorf(u), fv = floorf(v);
+    const float fx = u - fu, fy = v - fv;
+    const int iw = (int)w - 1, ih = (int)h - 1;
+    const int i0 = min(max((int)fu, 0), iw), j0 = min(max((int)fv, 0), ih);
+    const int i1 = min((int)fu + 1, iw), j1 = min((int)fv + 1, ih);
+    const float* r0 = lv + (size_t)j0 * w * 3 + ch;
+    const float* r1 = lv + (size_t)j1 * w * 3 + ch;
+    const float t00 = r0[3 * i0], t10 = r0[3 * i1], t01 = r1[3 * i0], t11 = r1[3 * i1];
+    const float top = t00 + fx * (t10 - t00);
+    const float bot = t01 + fx * (t11 - t01);
+    return top + fy * (bot - top);
+}
+
 // ---------------------------------------------------------------------------
 // Eq. 7's colour difference: both colours (linear RGB, sRGB primaries) to CIE
 // Lab (D65 white), then the CIE94 difference with graphic-arts weights and the

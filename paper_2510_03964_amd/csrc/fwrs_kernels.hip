@@ -10,14 +10,11 @@
 // candidate count m is the same for every pixel (each pixel receives exactly
 // one candidate per frame), so it is the context's frame count, not a plane.
 //
-// One thread per pixel; a block of 256 threads covers one work item laid out
-// as 1, 2 or 4 tiles of tile_x pixels by tile_y rows (the tile shape changes
-// the access pattern, never the results).  A pixel's loads that do not depend
-// on its decision (level, w_sum, the resolve plane or the record) are issued
-// first and overlap the Philox rounds and the weight; the colour and, where
-// needed, the record of a pixel that takes the candidate follow the decision.
-// The pass is bound by HBM traffic; there is no contraction anywhere, so no
-// matrix cores.
+// A block of 256 threads covers one work item of 256 pixels, laid out as 1, 2
+// or 4 tiles of tile_x pixels by tile_y rows (the tile shape changes the access
+// pattern, never the results).  Decisions run with one lane per pixel, the work
+// on records with one lane per slot (stream_tiles).  The passes are bound by
+// their traffic to memory; there is no contraction anywhere, so no matrix cores.
 //
 // Per pixel and frame (Sec. 4.1-4.2 of the paper):
 //   w    = Eq. 4 weight from the eccentricity to the gaze (level 0 -> 1)
@@ -26,15 +23,21 @@
 //   slot j takes (colour, w, t) when u_j * (W1' + w) > W1'   (Alg. 2)
 //   w_sum <- W1' + w
 //   out  = sum_j wt_j col_j / sum_j wt_j                      (resolve)
-// The new colour is read only by pixels in which some slot takes it; the
-// output is written with non-temporal stores (it is not read again here).
+// The new colour is read only by pixels in which some slot takes it (per-slot
+// modes: by every pixel).
 #include "fwrs_device.hpp"
 #include "fwrs_internal.hpp"
 
 // Which streams use non-temporal loads / stores (bits, see kNt* below); a
-// launch-shape tuning constant that never changes results.
+// launch-shape tuning constant that never changes results.  Level, colour,
+// w_sum and the output are streamed once a frame.  The resolve plane is not
+// among them: a changed pixel rewrites 12 bytes of a line that was just read,
+// and non-temporal partial stores go to memory one by one (scattered 12-byte
+// stores of 8% of the pixels: 22 us against 14).  Three 3840x2160 sessions in
+// turn, frame 60: 224 us with the plane non-temporal, 211 without, 233 with
+// nothing non-temporal; the stereo pair at k = 8 454, 422 and 448.
 #ifndef FWRS_NT_MASK
-#define FWRS_NT_MASK 0x3C7u
+#define FWRS_NT_MASK 0x0C7u
 #endif
 
 namespace fwrs {
@@ -168,13 +171,6 @@ __device__ __forceinline__ uint32_t decide_any(const FrameDesc& d, uint32_t p, f
     return mask;
 }
 
-// Whether the resolve plane is read before the decision (with the pixel's other
-// loads, so an unchanged pixel has it at hand) or only by unchanged pixels
-// after it; a scheduling choice that never changes results.
-#ifndef FWRS_RES_EARLY
-#define FWRS_RES_EARLY 1
-#endif
-
 // Slot-count argument of the per-pixel code: a count the code is compiled for
 // (its record in registers), 0 for any count (streamed slot by slot), or kWild:
 // any count with the general division, root and variate test, for the frames of
@@ -206,180 +202,6 @@ __device__ __forceinline__ void resolve_slots(const float4 (&r)[R], float& q0, f
     q0 = a0 * rs;
     q1 = a1 * rs;
     q2 = a2 * rs;
-}
-
-// ---------------------------------------------------------------------------
-// One pixel.  K > 0 keeps the pixel's whole record in registers; K == 0
-// (any slot count up to kMaxK) streams the record one slot at a time.
-// Returns the number of slots replaced plus 2^16 if there was any.
-// ---------------------------------------------------------------------------
-template <int SLOTS, int OP, bool FOV = false>
-__device__ __forceinline__ uint32_t pixel(const FrameDesc& d, uint32_t x, uint32_t y, const FovSrc* fs = nullptr)
-{
-    const uint32_t p = y * d.width + x;
-    constexpr bool kTame = SLOTS != kWild;
-    constexpr int K = SLOTS > 0 ? SLOTS : 0;
-    const int kk = K ? K : (int)d.k;
-    constexpr int R = K ? K : 1;
-    constexpr bool kUpdates = OP != kResolve;
-    constexpr bool kResolves = OP != kPush;
-    // every slot's record is read before the decision: the resolve needs them all
-    constexpr bool kEager = OP == kFused || OP == kFill || OP == kResolve;
-    // a recomputed resolve is also written to the resolve plane
-    constexpr bool kKeepsRes = OP == kCached || OP == kFill;
-    constexpr bool kResEarly = OP == kCached && FWRS_RES_EARLY;
-    float4* rec = reinterpret_cast<float4*>(d.rec) + (size_t)p * (size_t)kk;
-    uint32_t* idx = d.idx + (size_t)p * (size_t)kk;
-    const float* color = d.color + 3 * (size_t)p;
-    float* res = d.res + 3 * (size_t)p;
-    // Frame 0 of a context meets the empty store (every slot zero): nothing to read.
-    const bool empty = d.t == 0u;
-
-    // 1. every load that does not depend on this frame's decisions (the compiler's
-    //    own schedule interleaves them with step 2; forcing all of them ahead of
-    //    the arithmetic measured slower)
-    uint32_t lv = 0u;
-    float W1 = 0.f;
-    if (kUpdates) {
-        if constexpr (FOV) lv = fov_level(*fs, d.gx, d.gy, x, y);
-        else lv = ld<kNtLevel>(d.level + p);
-        W1 = ld<kNtWsumLd>(d.wsum + p);
-    }
-    float4 r[R];
-#pragma unroll
-    for (int j = 0; j < R; ++j) r[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (K && kEager && !empty) {
-#pragma unroll
-        for (int j = 0; j < R; ++j) r[j] = ld4<kNtRecLd>(rec + j);
-    }
-    float q0 = 0.f, q1 = 0.f, q2 = 0.f;
-    if (kResEarly) {
-        q0 = ld<kNtResLd>(res + 0);
-        q1 = ld<kNtResLd>(res + 1);
-        q2 = ld<kNtResLd>(res + 2);
-    }
-
-    // 2. arithmetic that needs no loaded value: the Philox words and the weight's geometry
-    Words<R> words;
-    float outside = 0.f, e = 0.f;
-    if (kUpdates) {
-        if (K) words = philox_words<R>(d, p);
-        const float dx = ((float)x + 0.5f) - d.gx;
-        const float dy = ((float)y + 0.5f) - d.gy;
-        outside = weight_outside<kTame>(d.c, dx * dx + dy * dy, e);
-    }
-
-    // 3. weight (Eq. 4), bias (Eq. 6) and the Alg. 2 decision per slot
-    uint32_t tk = 0u;
-    float w = 0.f, s = 0.f;
-    if (kUpdates) {
-        w = select_eq4(d.c, outside, e, lv);
-        const float W1b = bias_shared<kTame>(W1, w, d.bias, d.c.decay);
-        s = W1b + w;
-        tk = K ? decide_words<R>(words, W1b, s) : decide_any<kTame>(d, p, W1b, s);
-    }
-
-    // 4. the loads the decision calls for, all issued before any is waited for:
-    //    the records of the slots that keep their sample (where only now needed)
-    //    and the new colour, where some slot takes it; then the stores -- w_sum
-    //    and the replaced slots -- which thus delay none of these loads
-    if (K && (OP == kIncremental || OP == kCached) && tk && !empty) {
-#pragma unroll
-        for (int j = 0; j < R; ++j)
-            if (!((tk >> j) & 1u)) r[j] = ld4<kNtRecLd>(rec + j);
-    }
-    float c0 = 0.f, c1 = 0.f, c2 = 0.f;
-    if (tk) {
-        if constexpr (FOV) {
-            const float3 c = fov_colour(*fs, x, y, p, lv);
-            c0 = c.x;
-            c1 = c.y;
-            c2 = c.z;
-        } else {
-            c0 = ld<kNtColor>(color + 0);
-            c1 = ld<kNtColor>(color + 1);
-            c2 = ld<kNtColor>(color + 2);
-        }
-    }
-    if (kUpdates) st<kNtWsumSt>(d.wsum + p, s);
-    const float4 fresh = make_float4(w, c0, c1, c2);
-    if (K) {
-#pragma unroll
-        for (int j = 0; j < R; ++j)
-            if ((tk >> j) & 1u) r[j] = fresh;
-        if constexpr (K >= 8) {
-            // Each lane's next replaced slot per store instruction: a wave issues
-            // as many as its pixels' most replacements instead of one per slot,
-            // nearly all lanes masked off (3% faster at k = 8, 6% slower at k = 4).
-            for (uint32_t m = tk; m != 0u; m &= m - 1u) {
-                const uint32_t j = (uint32_t)__builtin_ctz(m);
-                st4<kNtRecSt>(rec + j, fresh);
-                st<kNtIdxSt>(idx + j, d.t);
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < R; ++j)
-                if ((tk >> j) & 1u) {
-                    st4<kNtRecSt>(rec + j, fresh);
-                    st<kNtIdxSt>(idx + j, d.t);
-                }
-        }
-    }
-
-    // 5. resolve: sum_j w_j col_j / sum_j w_j in slot order -- recomputed, or for a
-    //    pixel without a replacement the unchanged value (kCached: from the
-    //    resolve plane; kIncremental: the output already holds it)
-    if (kResolves) {
-        const bool recompute = (OP != kIncremental && OP != kCached) || tk != 0u;
-        float* o = d.out + 3 * (size_t)p;
-        if (recompute) {
-            if (K) {
-                resolve_slots<R>(r, q0, q1, q2);
-            } else {
-                float S = 0.f, a0 = 0.f, a1 = 0.f, a2 = 0.f;
-                for (int j = 0; j < kk; ++j) {
-                    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if ((tk >> j) & 1u) {
-                        v = fresh;
-                        st4<kNtRecSt>(rec + j, fresh);
-                        st<kNtIdxSt>(idx + j, d.t);
-                    } else if (!empty) {
-                        v = ld4<kNtRecLd>(rec + j);
-                    }
-                    S = S + v.x;
-                    a0 = a0 + v.x * v.y;
-                    a1 = a1 + v.x * v.z;
-                    a2 = a2 + v.x * v.w;
-                }
-                // S == 0 only before the first frame (every kept weight is > 0): output 0.
-                const float rs = resolve_scale<kTame>(S);
-                q0 = a0 * rs;
-                q1 = a1 * rs;
-                q2 = a2 * rs;
-            }
-            if (kKeepsRes) {
-                st<kNtResSt>(res + 0, q0);
-                st<kNtResSt>(res + 1, q1);
-                st<kNtResSt>(res + 2, q2);
-            }
-        } else if (OP == kCached && !kResEarly) {
-            q0 = ld<kNtResLd>(res + 0);
-            q1 = ld<kNtResLd>(res + 1);
-            q2 = ld<kNtResLd>(res + 2);
-        }
-        if (recompute || OP == kCached) {
-            st<kNtOut>(o + 0, q0);
-            st<kNtOut>(o + 1, q1);
-            st<kNtOut>(o + 2, q2);
-        }
-    } else if (!K) {
-        for (int j = 0; j < kk; ++j)
-            if ((tk >> j) & 1u) {
-                st4<kNtRecSt>(rec + j, fresh);
-                st<kNtIdxSt>(idx + j, d.t);
-            }
-    }
-    return __popc(tk) + (tk ? 0x10000u : 0u);
 }
 
 // ---------------------------------------------------------------------------
@@ -687,16 +509,6 @@ __device__ __forceinline__ bool item_pixel(const FrameDesc& d, uint32_t item, ui
     return item_pixel_of(d, item, __builtin_amdgcn_readfirstlane(tid >> 6), tid & 63u, x, y);
 }
 
-// One work item (256 pixels, one per thread).
-template <int K, int OP, bool PER_SLOT = false, bool FOV = false>
-__device__ __forceinline__ uint32_t process_item(const FrameDesc& d, uint32_t item, const FovSrc* fs = nullptr)
-{
-    uint32_t x, y;
-    if (!item_pixel(d, item, x, y)) return 0u;
-    if constexpr (PER_SLOT) return pixel_per_slot<K, OP, FOV>(d, x, y, fs);
-    return pixel<K, OP, FOV>(d, x, y, fs);
-}
-
 // Sum of v over the wave, in every lane: five row-wise steps by data-parallel
 // moves (no LDS traffic) and the last lane's total as a scalar.
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v)
@@ -730,12 +542,291 @@ __device__ __forceinline__ void add_stats_wide(unsigned long long* stats, uint32
     if (changed) add_counts(stats, wave_sum(slots), changed, 0u);
 }
 
+// The counts of stream_tiles, uniform over the wave.
+__device__ __forceinline__ void add_stats_uniform(unsigned long long* stats, uint32_t v)
+{
+    if (v) add_counts(stats, v & 0xFFFFu, v >> 16, 0u);
+}
+
 __device__ __forceinline__ void add_stats(unsigned long long* stats, uint32_t v)
 {
     // v = replaced slots + 2^16 * (pixel changed) + 2^24 * (pixel flushed); the wave sum
     // has at most 1024 slots and 64 pixels per field
     v = wave_sum(v);
     if (v) add_counts(stats, v & 0xFFFFu, (v >> 16) & 0xFFu, v >> 24);
+}
+
+// ---------------------------------------------------------------------------
+// A frame of a mode with one w_sum per pixel: T tiles of 64 pixels per wave.
+//  1. One lane per pixel: the loads every pixel needs (level, w_sum, for kCached
+//     its resolve from the plane), then the decision.  The pixels whose record is
+//     needed -- those that replace a slot, or all of them where every resolve is
+//     taken from the records (kFused, kFill, kResolve) -- go on a list in LDS.
+//  2. One lane per slot: groups of lanes work through the list, so a record
+//     (16k bytes) is one coalesced access instead of k accesses 16k bytes apart,
+//     and a wave holds only pixels that have work.
+//  3. One lane per pixel: w_sum and the output row, a listed pixel's resolve read
+//     back from the list, so rows leave whole.
+// The list is the wave's own, so no barrier is needed.  Stores come after the
+// loads of the same step, because vector-memory operations are waited for in
+// order.
+//
+// Why: the passes are bound by their requests to the memory side (128-byte reads,
+// 64-byte writes, about 6 TB/s of them) and by waiting; one lane per pixel with k
+// loads per record kept every line's requests pending in L1 k times.  Measured
+// against that form, per frame: k = 8 at 1920x1080 while a store fills 138 ->
+// 106 us, k = 4 71 -> 62 us, incremental 2560x1440 34.1 -> 23.6 us at frame 2000
+// and 48 -> 42 at frame 60, 3840x2160 85 -> 81 us at frame 2000 (482 MB of requests).
+// T: the ops without the plane's row (kIncremental, kPush) have few loads in
+// flight per tile and take two where that still leaves two rounds of resident
+// waves (2560x1440 at frame 2000: T = 1 27.9 us, 2 23.6, 4 23.3; 800x600, less
+// than one round: 10.3 and 11.0); the others are faster at one (3840x2160 at frame
+// 600: 100.5 us, 105.6, 107.8).
+// ---------------------------------------------------------------------------
+constexpr bool takes_two_tiles(int op) { return op == kIncremental || op == kPush; }
+constexpr uint32_t kTwoTilesItems = 4096u;      // items from which they do: 2 x 8192 resident waves
+
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Data-parallel moves within quads of lanes: lane a, b, c, d of the quad to its
+// four lanes.
+template <int A, int B, int C, int D>
+__device__ __forceinline__ float quad_perm(float v)
+{
+    constexpr int sel = A | (B << 2) | (C << 4) | (D << 6);
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), sel, 0xF, 0xF, true));
+}
+
+// Lanes of a pixel's group: one per slot, a power of two, whole quads from 3
+// slots on.
+template <int K>
+__device__ __forceinline__ uint32_t group_log2(uint32_t kk)
+{
+    return K == 1 ? 0u : K == 2 ? 1u : kk <= 4u ? 2u : kk <= 8u ? 3u : 4u;
+}
+
+// The group's first lane that has group_sum's result: lane 0, beyond 4 slots the
+// first lane of the last slot's quad.
+template <int K>
+__device__ __forceinline__ uint32_t group_first(uint32_t kk)
+{
+    return K == 1 || K == 2 ? 0u : (kk - 1u) & ~3u;
+}
+
+// 0 + v_0 + v_1 + ... + v_(kk-1) over a group of lanes, added in lane order (K: as
+// kk where known, else 0).  Valid in the quad of group_first.
+template <int K>
+__device__ __forceinline__ float group_sum(float v, uint32_t kk)
+{
+    float s = 0.f;
+    if constexpr (K == 1) {
+        s = s + v;
+    } else if constexpr (K == 2) {
+        s = s + quad_perm<0, 0, 2, 2>(v);
+        s = s + quad_perm<1, 1, 3, 3>(v);
+    } else {
+        const float v0 = quad_perm<0, 0, 0, 0>(v), v1 = quad_perm<1, 1, 1, 1>(v);
+        const float v2 = quad_perm<2, 2, 2, 2>(v), v3 = quad_perm<3, 3, 3, 3>(v);
+#pragma unroll
+        for (uint32_t j = 0; j < (K ? (uint32_t)K : (uint32_t)kMaxK); j += 4u) {
+            if (!K && j >= kk) break;
+            // the sum so far, from the quad below (row_shr:4)
+            if (j) s = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, s), 0x114, 0xF, 0xF, true));
+            s = s + v0;
+            if (K || j + 1u < kk) s = s + v1;
+            if (K || j + 2u < kk) s = s + v2;
+            if (K || j + 3u < kk) s = s + v3;
+        }
+    }
+    return s;
+}
+
+// The list's n pixels: entry {x, y, weight, replaced slots | level << 16}.  A
+// group of lanes takes a pixel, 64 / group pixels a round.  Replaced slots are
+// stored; where most pixels of a frame replace slots (kFused, kFill) a pixel that
+// replaces at least a quarter stores its whole record, because full lines are
+// written faster than parts of them (k = 8 while filling 108.9 -> 106.1 us a
+// 1920x1080 frame, k = 4 at 3840x2160 258 -> 250.6; 6% slower for kCached, whose
+// changed pixels are few).  The resolve goes to the list, for kCached also to the
+// plane; kIncremental writes the output here.  Returns the lane's replaced slots.
+// (Loading 2, 4 or 8 rounds ahead of the first: within 1% at 2, slower beyond,
+// for the registers.)
+template <int SLOTS, int OP, bool FOV>
+__device__ __forceinline__ uint32_t listed_pixels(const FrameDesc& d, const FovSrc* fs, uint4* list, uint32_t n)
+{
+    constexpr bool kTame = SLOTS != kWild;
+    constexpr int K = SLOTS > 0 ? SLOTS : 0;
+    constexpr bool kResolves = OP != kPush, kUpdates = OP != kResolve;
+    constexpr bool kWhole = OP == kFused || OP == kFill;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t kk = K ? (uint32_t)K : d.k;
+    const uint32_t lg = group_log2<K>(kk), first = group_first<K>(kk);
+    const uint32_t j = lane & ((1u << lg) - 1u), per = 64u >> lg;
+    const bool slot = K || j < kk;
+    const bool empty = d.t == 0u;                   // frame 0 meets the empty store: nothing to read
+    uint32_t taken = 0u;
+    for (uint32_t b = 0; b < n; b += per) {
+        const uint32_t at = b + (lane >> lg);
+        const bool own = at < n;
+        const uint4 entry = list[own ? at : b];     // past the end: an entry no result has replaced yet
+        const uint32_t p = entry.y * d.width + entry.x;
+        const size_t s = (size_t)p * kk + (slot ? j : 0u);
+        float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (kResolves && !empty) r = ld4<kNtRecLd>(reinterpret_cast<const float4*>(d.rec) + s);
+        bool take = false;
+        if constexpr (kUpdates) {
+            float c0, c1, c2;
+            if constexpr (K == 1 || K == 2) {
+                if constexpr (FOV) {
+                    const float3 c = fov_colour(*fs, entry.x, entry.y, p, entry.w >> 16);
+                    c0 = c.x;
+                    c1 = c.y;
+                    c2 = c.z;
+                } else {
+                    const float* color = d.color + 3 * (size_t)p;
+                    c0 = ld<kNtColor>(color + 0);
+                    c1 = ld<kNtColor>(color + 1);
+                    c2 = ld<kNtColor>(color + 2);
+                }
+            } else {                                // each lane of a quad loads one channel
+                const uint32_t ch = (j & 3u) < 3u ? (j & 3u) : 2u;
+                float c;
+                if constexpr (FOV) c = fov_channel(*fs, entry.x, entry.y, p, entry.w >> 16, ch);
+                else c = ld<kNtColor>(d.color + 3 * (size_t)p + ch);
+                c0 = quad_perm<0, 0, 0, 0>(c);
+                c1 = quad_perm<1, 1, 1, 1>(c);
+                c2 = quad_perm<2, 2, 2, 2>(c);
+            }
+            take = slot && ((entry.w >> j) & 1u) != 0u;
+            if (take) r = make_float4(__builtin_bit_cast(float, entry.z), c0, c1, c2);
+        }
+        float q0 = 0.f, q1 = 0.f, q2 = 0.f;
+        if constexpr (kResolves) {
+            const float rs = resolve_scale<kTame>(group_sum<K>(r.x, kk));
+            q0 = group_sum<K>(r.x * r.y, kk) * rs;
+            q1 = group_sum<K>(r.x * r.z, kk) * rs;
+            q2 = group_sum<K>(r.x * r.w, kk) * rs;
+        }
+        if (own) {
+            const bool whole = kWhole && slot && 4u * (uint32_t)__popc(entry.w & 0xFFFFu) >= kk;
+            if (take || whole) st4<kNtRecSt>(reinterpret_cast<float4*>(d.rec) + s, r);
+            if (take) {
+                st<kNtIdxSt>(d.idx + s, d.t);
+                taken += 1u;
+            }
+            if constexpr (OP == kCached || OP == kIncremental) {
+                float* to = (OP == kCached ? d.res : d.out) + 3 * (size_t)p;
+                constexpr uint32_t bit = OP == kCached ? kNtResSt : 0u;    // scattered: never non-temporal
+                if constexpr (K == 1 || K == 2) {
+                    if (j == 0u) {
+                        st<bit>(to + 0, q0);
+                        st<bit>(to + 1, q1);
+                        st<bit>(to + 2, q2);
+                    }
+                } else if (j >= first && j < first + 3u) {
+                    st<bit>(to + (j - first), j == first ? q0 : j == first + 1u ? q1 : q2);
+                }
+            }
+            if (kResolves && OP != kIncremental && j == first)
+                list[at] = make_uint4(__builtin_bit_cast(uint32_t, q0), __builtin_bit_cast(uint32_t, q1),
+                                      __builtin_bit_cast(uint32_t, q2), 0u);
+        }
+    }
+    return taken;
+}
+
+// The wave's 64 T pixels of work items item0 .. item0 + T - 1; list has room for
+// 64 T entries.  Returns the wave's (uniform) replaced slots + 2^16 x changed pixels.
+template <int SLOTS, int OP, int T, bool FOV = false>
+__device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t item0, uint32_t wave, uint4* list,
+                                                 const FovSrc* fs = nullptr)
+{
+    constexpr bool kTame = SLOTS != kWild;
+    constexpr int K = SLOTS > 0 ? SLOTS : 0;
+    constexpr bool kUpdates = OP != kResolve;
+    constexpr bool kAll = OP == kFused || OP == kFill || OP == kResolve;    // every pixel is listed
+    constexpr bool kRow = OP == kCached || kAll;                            // the output leaves by rows
+    const uint32_t lane = threadIdx.x & 63u;
+
+    uint32_t x[T], y[T], p[T], lv[T], at[T];
+    bool in[T];
+    float W[T], q0[T], q1[T], q2[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        in[t] = item_pixel_of(d, item0 + t, wave, lane, x[t], y[t]);
+        p[t] = in[t] ? y[t] * d.width + x[t] : 0u;          // lanes outside read pixel 0 and store nothing
+        lv[t] = 0u;
+        if constexpr (kUpdates) {
+            if constexpr (FOV) lv[t] = fov_level(*fs, d.gx, d.gy, x[t], y[t]);
+            else lv[t] = ld<kNtLevel>(d.level + p[t]);
+            W[t] = ld<kNtWsumLd>(d.wsum + p[t]);
+        }
+        if constexpr (OP == kCached) {
+            const float* res = d.res + 3 * (size_t)p[t];
+            q0[t] = ld<kNtResLd>(res + 0);
+            q1[t] = ld<kNtResLd>(res + 1);
+            q2[t] = ld<kNtResLd>(res + 2);
+        }
+    }
+    uint32_t n = 0u, changed = 0u;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        uint32_t tk = 0u;
+        float w = 0.f;
+        if constexpr (kUpdates) {
+            const float dx = ((float)x[t] + 0.5f) - d.gx;
+            const float dy = ((float)y[t] + 0.5f) - d.gy;
+            w = weight_eq4<kTame>(d.c, dx * dx + dy * dy, lv[t]);
+            const float W1b = bias_shared<kTame>(W[t], w, d.bias, d.c.decay);
+            const float s = W1b + w;
+            if constexpr (K > 0) tk = decide_words<K>(philox_words<K>(d, p[t]), W1b, s);
+            else tk = decide_any<kTame>(d, p[t], W1b, s);
+            if (!in[t]) tk = 0u;
+            W[t] = s;
+        }
+        const uint64_t took = __ballot(tk != 0u), mask = kAll ? __ballot(in[t]) : took;
+        changed += (uint32_t)__builtin_popcountll(took);
+        at[t] = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+        if (kAll ? in[t] : tk != 0u)
+            list[at[t]] = make_uint4(x[t], y[t], __builtin_bit_cast(uint32_t, w), tk | (lv[t] << 16));
+        else
+            at[t] = 0xFFFFFFFFu;
+        n += (uint32_t)__builtin_popcountll(mask);
+    }
+    wave_lds_fence();
+    uint32_t slots = 0u;
+    if (n) slots = listed_pixels<SLOTS, OP, FOV>(d, fs, list, n);
+    if (changed) slots = wave_sum(slots);
+    wave_lds_fence();
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        if (!in[t]) continue;
+        if constexpr (kUpdates) st<kNtWsumSt>(d.wsum + p[t], W[t]);
+        if constexpr (kRow) {
+            if (at[t] != 0xFFFFFFFFu) {
+                const uint4 v = list[at[t]];
+                q0[t] = __builtin_bit_cast(float, v.x);
+                q1[t] = __builtin_bit_cast(float, v.y);
+                q2[t] = __builtin_bit_cast(float, v.z);
+            }
+            float* o = d.out + 3 * (size_t)p[t];
+            st<kNtOut>(o + 0, q0[t]);
+            st<kNtOut>(o + 1, q1[t]);
+            st<kNtOut>(o + 2, q2[t]);
+            if constexpr (OP == kFill) {
+                float* res = d.res + 3 * (size_t)p[t];
+                st<kNtResSt>(res + 0, q0[t]);
+                st<kNtResSt>(res + 1, q1[t]);
+                st<kNtResSt>(res + 2, q2[t]);
+            }
+        }
+    }
+    return slots + (changed << 16);
 }
 
 // Work items are visited in reverse order on odd frames, so each frame starts
@@ -747,11 +838,29 @@ __device__ __forceinline__ uint32_t frame_item(uint32_t block, uint32_t items, u
     return (t & 1u) ? items - 1u - block : block;
 }
 
-template <int K, int OP, bool PER_SLOT = false>
-__global__ __launch_bounds__(kBlock) void frame_kernel(FrameDesc d)
+// Work items [T block, T block + T) of a frame (per-slot modes: T = 1).
+template <int K, int OP, bool PER_SLOT, int T, bool FOV>
+__device__ __forceinline__ void frame_block(const FrameDesc& d, uint32_t block, const FovSrc* fs)
 {
-    const uint32_t n = process_item<K, OP, PER_SLOT>(d, frame_item(blockIdx.x, d.items, d.t));
-    if (OP != kResolve && d.stats) add_stats(d.stats, n);
+    if constexpr (PER_SLOT) {
+        uint32_t x, y, n = 0u;
+        if (item_pixel(d, block, x, y)) n = pixel_per_slot<K, OP, FOV>(d, x, y, fs);
+        if (d.stats) add_stats(d.stats, n);
+    } else {
+        __shared__ uint4 list[kBlock / 64][64 * T];
+        const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const uint32_t n = stream_tiles<K, OP, T, FOV>(d, T * block, wave, list[wave], fs);
+        if (OP != kResolve && d.stats) add_stats_uniform(d.stats, n);
+    }
+}
+
+// Waves per SIMD the frame kernels are compiled for (per-slot modes: no bound).
+constexpr int frame_waves(bool per_slot) { return per_slot ? 1 : 8; }
+
+template <int K, int OP, bool PER_SLOT = false, int T = 1>
+__global__ __launch_bounds__(kBlock, frame_waves(PER_SLOT)) void frame_kernel(FrameDesc d)
+{
+    frame_block<K, OP, PER_SLOT, T, false>(d, frame_item(blockIdx.x, gridDim.x, d.t), nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -775,37 +884,41 @@ __global__ __launch_bounds__(kBlock) void frame_kernel(FrameDesc d)
 // frames in turn through the store, every pixel in the same thread, so each
 // frame reads what the one before wrote.
 // ---------------------------------------------------------------------------
-template <int K, int OP, bool PER_SLOT = false>
-__device__ __forceinline__ uint32_t process_wave(const FrameDesc& d, uint32_t item, uint32_t wave)
+// One wave's share of a lone frame's work item; counts its replaced slots and
+// changed pixels.
+__device__ __forceinline__ void tick_item(const FrameDesc& d, uint32_t local, uint32_t wave, uint4* list)
 {
-    uint32_t x, y;
-    if (!item_pixel_of(d, item, wave, threadIdx.x & 63u, x, y)) return 0u;
-    if constexpr (PER_SLOT) return pixel_per_slot<K, OP>(d, x, y);
-    return pixel<K, OP>(d, x, y);
-}
-
-__device__ __forceinline__ uint32_t tick_item(const FrameDesc& d, uint32_t local, uint32_t wave)
-{
-    if (per_slot_mode(d.bias))
-        return d.tame ? process_wave<0, kFused, true>(d, local, wave) : process_wave<kWild, kFused, true>(d, local, wave);
-#define FWRS_TICK_OPS(KK)                                                                  \
-    return d.op == kCached ? process_wave<KK, kCached>(d, local, wave)                     \
-         : d.op == kFill ? process_wave<KK, kFill>(d, local, wave) : process_wave<KK, kFused>(d, local, wave)
-    if (!d.tame) FWRS_TICK_OPS(kWild);
-    switch (d.k) {
-        case 1: FWRS_TICK_OPS(1);
-        case 2: FWRS_TICK_OPS(2);
-        case 4: FWRS_TICK_OPS(4);
-        case 8: FWRS_TICK_OPS(8);
-        default: FWRS_TICK_OPS(0);
+    if (per_slot_mode(d.bias)) {
+        uint32_t x, y, n = 0u;
+        if (item_pixel_of(d, local, wave, threadIdx.x & 63u, x, y))
+            n = d.tame ? pixel_per_slot<0, kFused>(d, x, y) : pixel_per_slot<kWild, kFused>(d, x, y);
+        if (d.stats) add_stats(d.stats, n);
+        return;
+    }
+    uint32_t n = 0u;
+#define FWRS_TICK_OPS(KK)                                                        \
+    n = d.op == kCached ? stream_tiles<KK, kCached, 1>(d, local, wave, list)     \
+      : d.op == kFill ? stream_tiles<KK, kFill, 1>(d, local, wave, list)         \
+                      : stream_tiles<KK, kFused, 1>(d, local, wave, list)
+    if (!d.tame) {
+        FWRS_TICK_OPS(kWild);
+    } else {
+        switch (d.k) {
+            case 1: FWRS_TICK_OPS(1); break;
+            case 2: FWRS_TICK_OPS(2); break;
+            case 4: FWRS_TICK_OPS(4); break;
+            case 8: FWRS_TICK_OPS(8); break;
+            default: FWRS_TICK_OPS(0); break;
+        }
     }
 #undef FWRS_TICK_OPS
+    if (d.stats) add_stats_uniform(d.stats, n);
 }
 
 // One work item of a group of d.nf > 1 frames (d its leader); G as tick_kernel's.
 template <int G>
 __device__ __forceinline__ void tick_group_item(const FrameDesc& d, const FrameDesc* __restrict__ descs,
-                                                uint32_t local, uint32_t wave)
+                                                uint32_t local, uint32_t wave, uint4* list)
 {
     const FrameDesc* later = descs + d.more;
     if (d.op == kGroup) {
@@ -825,8 +938,7 @@ __device__ __forceinline__ void tick_group_item(const FrameDesc& d, const FrameD
     }
     for (uint32_t f = 0; f < d.nf; ++f) {
         const FrameDesc& df = f == 0u ? d : later[f - 1u];
-        const uint32_t v = tick_item(df, local, wave);
-        if (df.stats) add_stats(df.stats, v);
+        tick_item(df, local, wave, list);
     }
 }
 
@@ -851,17 +963,17 @@ __device__ __forceinline__ void tick_blocks(const TickHead& head, const FrameDes
     uint32_t local = item - d.first;
     if (d.rev) local = d.items - 1u - local;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (G != kTickAlone && d.nf > 1u) {
-        tick_group_item<G>(d, descs, local, wave);
-    } else {
-        const uint32_t v = tick_item(d, local, wave);
-        if (d.stats) add_stats(d.stats, v);
-    }
+    __shared__ uint4 list[kBlock / 64][64];
+    if (G != kTickAlone && d.nf > 1u) tick_group_item<G>(d, descs, local, wave, list[wave]);
+    else tick_item(d, local, wave, list[wave]);
 }
+
+// Waves per SIMD the kernels are compiled for.
+constexpr int tick_waves(int kind) { return kind == kTickGroups8 ? 5 : kind == kTickGroups ? 7 : 8; }
 
 // The table in device memory.
 template <int G>
-__global__ __launch_bounds__(kBlock) void tick_kernel(const TickHead* __restrict__ head,
+__global__ __launch_bounds__(kBlock, tick_waves(G)) void tick_kernel(const TickHead* __restrict__ head,
                                                       const FrameDesc* __restrict__ descs)
 {
     tick_blocks<G>(*head, descs);
@@ -871,7 +983,7 @@ __global__ __launch_bounds__(kBlock) void tick_kernel(const TickHead* __restrict
 // frames), read in place from the kernel-argument segment: indexing the
 // by-value parameter itself would copy it to private memory first.
 template <int G>
-__global__ __launch_bounds__(kBlock) void tick_args_kernel(const TickArgs a)
+__global__ __launch_bounds__(kBlock, tick_waves(G)) void tick_args_kernel(const TickArgs a)
 {
     (void)a;
     const TickArgs* in = (const TickArgs*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -1344,10 +1456,9 @@ __global__ __launch_bounds__(kBlock) void foveate_kernel(FoveateArgs a)
 }
 
 template <int K, bool PER_SLOT, int OP>
-__global__ __launch_bounds__(kBlock) void foveated_kernel(FovDesc fd)
+__global__ __launch_bounds__(kBlock, frame_waves(PER_SLOT)) void foveated_kernel(FovDesc fd)
 {
-    const uint32_t n = process_item<K, OP, PER_SLOT, true>(fd.f, frame_item(blockIdx.x, fd.f.items, fd.f.t), &fd.s);
-    if (fd.f.stats) add_stats(fd.f.stats, n);
+    frame_block<K, OP, PER_SLOT, 1, true>(fd.f, frame_item(blockIdx.x, gridDim.x, fd.f.t), &fd.s);
 }
 
 __global__ void fill_u32_kernel(uint32_t* __restrict__ p, size_t n, uint32_t v)
@@ -1362,15 +1473,29 @@ __global__ void fill_u32_kernel(uint32_t* __restrict__ p, size_t n, uint32_t v)
 // The per-pixel code's slot-count argument for a frame.
 static int slots_arg(const FrameDesc& d) { return d.tame ? (int)d.k : kWild; }
 
+template <int OP, int T>
+static hipError_t launch_shared(const FrameDesc& d, hipStream_t stream)
+{
+    const dim3 grid((d.items + (uint32_t)T - 1u) / (uint32_t)T), block(kBlock);
+    switch (slots_arg(d)) {
+        case kWild: hipLaunchKernelGGL((frame_kernel<kWild, OP, false, T>), grid, block, 0, stream, d); break;
+        case 1: hipLaunchKernelGGL((frame_kernel<1, OP, false, T>), grid, block, 0, stream, d); break;
+        case 2: hipLaunchKernelGGL((frame_kernel<2, OP, false, T>), grid, block, 0, stream, d); break;
+        case 4: hipLaunchKernelGGL((frame_kernel<4, OP, false, T>), grid, block, 0, stream, d); break;
+        case 8: hipLaunchKernelGGL((frame_kernel<8, OP, false, T>), grid, block, 0, stream, d); break;
+        default: hipLaunchKernelGGL((frame_kernel<0, OP, false, T>), grid, block, 0, stream, d); break;
+    }
+    return hipGetLastError();
+}
+
 template <int OP>
 static hipError_t launch_frame_op(const FrameDesc& d, hipStream_t stream)
 {
-    const dim3 grid(d.items), block(kBlock);
-    const int slots = slots_arg(d);
     // the per-slot modes keep no resolve plane: they run kPush, kFused or kIncremental
     if constexpr (OP == kPush || OP == kFused || OP == kIncremental) {
         if (per_slot_mode(d.bias)) {
-            switch (slots) {
+            const dim3 grid(d.items), block(kBlock);
+            switch (slots_arg(d)) {
                 case kWild: hipLaunchKernelGGL((frame_kernel<kWild, OP, true>), grid, block, 0, stream, d); break;
                 case 4: hipLaunchKernelGGL((frame_kernel<4, OP, true>), grid, block, 0, stream, d); break;
                 case 8: hipLaunchKernelGGL((frame_kernel<8, OP, true>), grid, block, 0, stream, d); break;
@@ -1379,15 +1504,10 @@ static hipError_t launch_frame_op(const FrameDesc& d, hipStream_t stream)
             return hipGetLastError();
         }
     }
-    switch (slots) {
-        case kWild: hipLaunchKernelGGL((frame_kernel<kWild, OP>), grid, block, 0, stream, d); break;
-        case 1: hipLaunchKernelGGL((frame_kernel<1, OP>), grid, block, 0, stream, d); break;
-        case 2: hipLaunchKernelGGL((frame_kernel<2, OP>), grid, block, 0, stream, d); break;
-        case 4: hipLaunchKernelGGL((frame_kernel<4, OP>), grid, block, 0, stream, d); break;
-        case 8: hipLaunchKernelGGL((frame_kernel<8, OP>), grid, block, 0, stream, d); break;
-        default: hipLaunchKernelGGL((frame_kernel<0, OP>), grid, block, 0, stream, d); break;
+    if constexpr (takes_two_tiles(OP)) {
+        if (d.items >= kTwoTilesItems) return launch_shared<OP, 2>(d, stream);
     }
-    return hipGetLastError();
+    return launch_shared<OP, 1>(d, stream);
 }
 
 hipError_t launch_frame(const FrameDesc& d, int op, hipStream_t stream)
@@ -1503,8 +1623,8 @@ hipError_t launch_foveate(const FovSrc& s, float* color, uint8_t* level, uint32_
 hipError_t launch_foveated(const FovDesc& fd, int op, hipStream_t stream)
 {
     if (fd.f.items == 0u) return hipSuccess;
-    const dim3 grid(fd.f.items), block(kBlock);
     const bool ps = per_slot_mode(fd.f.bias);
+    const dim3 grid(fd.f.items), block(kBlock);
 #define FWRS_FOV_LAUNCH(KK, PS, OPV) hipLaunchKernelGGL((foveated_kernel<KK, PS, OPV>), grid, block, 0, stream, fd)
 #define FWRS_FOV_OPS(KK)                                      \
     do {                                                      \
