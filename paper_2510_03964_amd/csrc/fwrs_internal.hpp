@@ -13,7 +13,7 @@ constexpr int kMaxK = 16;
 constexpr int kMaxBlurRadius = 32;
 constexpr int kGaussR1 = 3;             // ceil(3 sigma) of the Gaussian levels, sigma = 1 and 2
 constexpr int kGaussR2 = 6;
-constexpr int kGaussCols = 64;          // columns (threads) per block of the Gaussian level kernel
+constexpr int kGaussCols = 256;         // float columns (threads) per block of the Gaussian level kernel
 
 // The kernels' ops (the launchers take them as int).
 constexpr int kOpPush = 1;          // update only

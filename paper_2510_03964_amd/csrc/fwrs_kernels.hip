@@ -1276,50 +1276,93 @@ __global__ __launch_bounds__(kBlock) void mip_kernel(MipArgs a)
 
 // Gaussian levels from one read of the frame, into one plane: every pixel of
 // level l >= 1 gets the frame blurred with sigma 2^(l-1) (radius kGaussR1 or
-// kGaussR2) at that pixel; level-0 pixels are not written.  A block owns COLS
-// columns (one per thread) and a strip of ROWS output rows.  It walks the
-// strip's rows and a halo of kGaussR2 rows above and below (row indices clamped
-// to the image): each row segment, columns x0 - kGaussR2 .. x0 + COLS - 1 +
-// kGaussR2 (clamped), is staged in LDS as three channel planes; every thread
-// takes the horizontal sums of the radii the block needs at its column and
-// keeps the last rows' sums in registers; an output row's vertical sum is taken
-// once its last tap row is in.  The loads of the next rows are in flight while
-// the current row is summed.  Sums start at zero and add the taps in offset order,
-// the order of two separate passes (horizontal, then vertical).  Which levels
-// a block needs comes from its rectangle's distances to the gaze, widened by
-// 2^-10 relative so that rounding can only make it need more.
+// kGaussR2) at that pixel; level-0 pixels are not written.  The channels are
+// independent, so a row is W * 3 floats and a thread owns one float column: a
+// block owns kGaussCols of them and a strip of ROWS output rows, and walks the
+// strip's rows and a halo of kGaussR2 rows above and below (clamped to the
+// image) in batches of kGaussBatch: a batch is staged in LDS with its halo of
+// 3 kGaussR2 floats on either side (pixels clamped) while the next one is being
+// loaded, one barrier a batch.
+//
+// Sums start at zero and add the taps in offset order, horizontally, then
+// vertically, each product rounded.  The vertical sums are kept per output row
+// in progress: when a row's horizontal sum h arrives, it is tap i of the output
+// row i rows further up for every i, so acc[i] = acc[i - 1] + g[i] h moves every
+// sum one tap on (no register moves), and the weights' symmetry leaves 7 products
+// for the 13 taps.  A column thread thus takes 13 + 13 operations across and
+// 7 + 13 down per row.  Which levels a block needs comes from its rectangle's
+// distances to the gaze, widened by 2^-10 relative so that rounding can only make
+// it need more.
+//
+// Bound by LDS reads (13 of 4 bytes per float and row at radius 6), next by the
+// vector ALU (a fused multiply-add would round differently).  One thread per pixel
+// column with a window of row sums took 276 instructions per pixel and walked row,
+// and its few waves left the chip idle below 4K.  The generator call at 2560x1440
+// went from 68 to 51 us (these levels 53 to 36), at 1920x1080 from 42 to 33, at
+// 256x256 from 20 to 9.5, at 3840x2160 from 121 to 104.  Four neighbouring floats
+// per lane read 2.6 times less LDS but leave 1.3 waves per SIMD at 2560x1440 (52 us;
+// 99 at 3840x2160); two floats: 57 and 117; the two levels in blocks of their own:
+// 51 and 108.
 struct GaussArgs {
     const float* src;
     float* dst;
     uint32_t w, h, cols;                               // cols: blocks per strip
     float gx, gy, r0sq, r1sq;
-    float g1[2 * kGaussR1 + 1];
-    float g2[2 * kGaussR2 + 1];
+    float g1[kGaussR1 + 1];                            // weights of offsets 0 .. R (symmetric)
+    float g2[kGaussR2 + 1];
 };
 
-template <int ROWS, int COLS>
-__global__ __launch_bounds__(COLS) void gauss_levels_kernel(GaussArgs a)
+constexpr int kGaussBatch = 4;
+
+// The vertical sums of radius R after one more row: acc[i] is the sum, taps 0 to
+// i, of the output row for which this row is tap i; returns the one that is
+// complete.
+template <int R>
+__device__ __forceinline__ float gauss_down(float (&acc)[2 * R], const float (&g)[R + 1], float h)
 {
-    constexpr int R1 = kGaussR1, R2 = kGaussR2;
-    constexpr int PF = 2;                              // rows in flight
-    constexpr int SEG = COLS + 2 * R2;                 // pixels of a staged row segment
-    constexpr int NF = 3 * SEG;                        // floats of it
-    constexpr int PER = (NF + COLS - 1) / COLS;        // floats staged per thread
+    float m[R + 1];
+#pragma unroll
+    for (int i = 0; i <= R; ++i) m[i] = g[i] * h;      // offset -i and i
+    const float done = acc[2 * R - 1] + m[R];
+#pragma unroll
+    for (int i = 2 * R - 1; i > 0; --i) acc[i] = acc[i - 1] + m[i < R ? R - i : i - R];
+    acc[0] = 0.0f + m[R];
+    return done;
+}
+
+// The horizontal sums of radius R of a batch's rows around float c of each
+// (floats of one channel are 3 apart), the rows' chains of additions side by side.
+template <int R, int B, int SEG>
+__device__ __forceinline__ void gauss_across(const float (*rows)[SEG], int c, const float (&g)[R + 1], float (&t)[B])
+{
+#pragma unroll
+    for (int u = 0; u < B; ++u) t[u] = 0.0f;
+#pragma unroll
+    for (int i = -R; i <= R; ++i)
+#pragma unroll
+        for (int u = 0; u < B; ++u) t[u] = t[u] + g[i < 0 ? -i : i] * rows[u][c + 3 * i];
+}
+
+template <int ROWS>
+__global__ __launch_bounds__(kGaussCols) void gauss_levels_kernel(GaussArgs a)
+{
+    constexpr int R1 = kGaussR1, R2 = kGaussR2, B = kGaussBatch;
+    constexpr int SEG = kGaussCols + 6 * R2;           // floats of a staged row
     constexpr int NV = ROWS + 2 * R2;                  // rows walked (halo included)
-    static_assert(R1 <= R2, "the sigma-1 taps are a subset of the sigma-2 taps");
-    static_assert(NV % PF == 0 && PF % 2 == 0, "whole, even prefetch groups");
-    __shared__ float seg[2][3 * SEG];
+    static_assert(NV % B == 0 && 6 * R2 <= kGaussCols, "whole batches; the halo is one extra float per thread at most");
+    __shared__ float seg[2][B][SEG];
 
     const int tid = (int)threadIdx.x;
     const int W = (int)a.w, H = (int)a.h;
     const uint32_t bx = blockIdx.x % a.cols, by = blockIdx.x / a.cols;   // one-dimensional grid, row-major
-    const int x0 = (int)bx * COLS, y0 = (int)by * ROWS;
-    const int x = x0 + tid;
+    const int f0 = (int)bx * kGaussCols, y0 = (int)by * ROWS;
+    const int x = (f0 + tid) / 3;
+    const bool own = x < W;
 
     // Levels present in the block's pixels (block-uniform, conservative).
     bool need1, need2;
     {
-        const float xa = (float)x0 + 0.5f, xb = (float)min(x0 + COLS, W) - 0.5f;
+        const float xa = (float)(f0 / 3) + 0.5f, xb = (float)min((f0 + kGaussCols - 1) / 3, W - 1) + 0.5f;
         const float ya = (float)y0 + 0.5f, yb = (float)min(y0 + ROWS, H) - 0.5f;
         const float nx = fminf(fmaxf(a.gx, xa), xb) - a.gx, ny = fminf(fmaxf(a.gy, ya), yb) - a.gy;
         const float fx = fmaxf(fabsf(xa - a.gx), fabsf(xb - a.gx)), fy = fmaxf(fabsf(ya - a.gy), fabsf(yb - a.gy));
@@ -1329,107 +1372,73 @@ __global__ __launch_bounds__(COLS) void gauss_levels_kernel(GaussArgs a)
     }
     if (!need1 && !need2) return;                      // every pixel at level 0
 
-    // This thread stages floats f = tid + q COLS of a segment: channel f % 3
-    // of segment pixel f / 3 (image column x0 - R2 + f / 3, clamped).
-    int goff[PER], loff[PER];
+    // Staged float e = tid (and kGaussCols + tid in the halo) is float f0 - 3 R2 + e
+    // of the row, its pixel clamped.
+    auto column = [&](int e) {
+        const int fs = f0 + e, px = fs / 3 - R2;
+        return min(max(px, 0), W - 1) * 3 + fs % 3;
+    };
+    const int off0 = column(tid);
+    const bool extra = tid < 6 * R2;
+    const int off1 = extra ? column(kGaussCols + tid) : off0;
+    float stage[B], halo[B];
+    auto fetch = [&](int vb) {
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int f = tid + q * COLS;
-        const int e = f / 3, ch = f - 3 * e;
-        const int xx = min(max(x0 - R2 + e, 0), W - 1);
-        goff[q] = xx * 3 + ch;
-        loff[q] = f < NF ? ch * SEG + e : -1;
-    }
-    // Walked row v is loaded into stage[v % PF] PF rows ahead: rows v + 1 ..
-    // v + PF are in flight while row v is summed (the loop is unrolled by PF,
-    // so every index is a constant and the ring stays in registers).
-    float stage[PF][PER];
-    auto fetch = [&](int v, float* dst) {
-        const int yy = min(max(y0 - R2 + v, 0), H - 1);
-        const float* row = a.src + (size_t)yy * (size_t)W * 3;
-#pragma unroll
-        for (int q = 0; q < PER; ++q)
-            if (loff[q] >= 0) dst[q] = row[goff[q]];
+        for (int u = 0; u < B; ++u) {
+            const int yy = min(max(y0 - R2 + vb + u, 0), H - 1);
+            const float* row = a.src + (size_t)yy * (size_t)W * 3;
+            stage[u] = row[off0];
+            halo[u] = extra ? row[off1] : 0.f;
+        }
     };
 
-    float3 h2[2 * R2 + 1];     // sigma-2 horizontal sums of walked rows v - 2 R2 .. v (oldest first)
-    float3 h1[2 * R1 + 1];     // sigma-1 horizontal sums of walked rows v - 2 R1 .. v
-#pragma unroll
-    for (int u = 0; u < PF; ++u) fetch(u, stage[u]);
-    for (int vb = 0; vb < NV; vb += PF) {
-#pragma unroll
-      for (int u = 0; u < PF; ++u) {
-        const int v = vb + u;
-        float* s = seg[u & 1];                         // PF is even: u & 1 == v & 1
-#pragma unroll
-        for (int q = 0; q < PER; ++q)
-            if (loff[q] >= 0) s[loff[q]] = stage[u][q];
-        __syncthreads();
-        if (v + PF < NV) fetch(v + PF, stage[u]);
+    const float dx = ((float)x + 0.5f) - a.gx;
+    const float dx2 = dx * dx;
+    // The finished sum o of image row y goes out where the pixel is at this level.
+    auto store = [&](int y, uint32_t level, float o) {
+        const float dy = ((float)y + 0.5f) - a.gy;     // ring_level
+        const float d2 = dx2 + dy * dy;
+        const uint32_t at = d2 <= a.r0sq ? 0u : (d2 <= a.r1sq ? 1u : 2u);
+        if (own && at == level) (a.dst + (size_t)y * (size_t)W * 3 + f0)[tid] = o;
+    };
 
-        const float* c = s + tid;                      // c[ch SEG + i]: channel ch, column x - R2 + i
+    float acc1[2 * R1], acc2[2 * R2];
+#pragma unroll
+    for (int i = 0; i < 2 * R1; ++i) acc1[i] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 2 * R2; ++i) acc2[i] = 0.f;
+    fetch(0);
+    for (int vb = 0; vb < NV; vb += B) {
+        float(*s)[SEG] = seg[(vb / B) & 1];
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            s[u][tid] = stage[u];
+            if (extra) s[u][kGaussCols + tid] = halo[u];
+        }
+        __syncthreads();                               // also: the other buffer's readers are done with it
+        if (vb + B < NV) fetch(vb + B);
+        // walked row v is image row y0 - R2 + v (clamped), the last tap of the row R further up
+        float h[B];
         if (need2) {
+            gauss_across<R2, B, SEG>(s, tid + 3 * R2, a.g2, h);
 #pragma unroll
-            for (int i = 0; i < 2 * R2; ++i) h2[i] = h2[i + 1];
-            float t[3];
+            for (int u = 0; u < B; ++u) h[u] = gauss_down<R2>(acc2, a.g2, h[u]);
 #pragma unroll
-            for (int ch = 0; ch < 3; ++ch) {
-                float acc = 0.f;
-#pragma unroll
-                for (int i = 0; i <= 2 * R2; ++i) acc = acc + a.g2[i] * c[ch * SEG + i];
-                t[ch] = acc;
+            for (int u = 0; u < B; ++u) {
+                const int v = vb + u, y = y0 + v - 2 * R2;
+                if (v >= 2 * R2 && y < H) store(y, 2u, h[u]);
             }
-            h2[2 * R2] = make_float3(t[0], t[1], t[2]);
         }
         if (need1) {
+            gauss_across<R1, B, SEG>(s, tid + 3 * R2, a.g1, h);
 #pragma unroll
-            for (int i = 0; i < 2 * R1; ++i) h1[i] = h1[i + 1];
-            float t[3];
+            for (int u = 0; u < B; ++u) h[u] = gauss_down<R1>(acc1, a.g1, h[u]);
 #pragma unroll
-            for (int ch = 0; ch < 3; ++ch) {
-                float acc = 0.f;
-#pragma unroll
-                for (int i = 0; i <= 2 * R1; ++i) acc = acc + a.g1[i] * c[ch * SEG + R2 - R1 + i];
-                t[ch] = acc;
+            for (int u = 0; u < B; ++u) {
+                const int v = vb + u, y = y0 + v - R1 - R2;
+                if (v >= R1 + R2 && v < R1 + R2 + ROWS && y < H) store(y, 1u, h[u]);
             }
-            h1[2 * R1] = make_float3(t[0], t[1], t[2]);
         }
-
-        // Walked row j is image row y0 - R2 + j (clamped); its radius-r sums
-        // are complete once walked row j + r is in, i.e. at v = j + r.
-        const int y1 = y0 + v - R1 - R2;
-        if (need1 && v >= R1 + R2 && v < R1 + R2 + ROWS && y1 < H && x < W &&
-            ring_level(a.r0sq, a.r1sq, a.gx, a.gy, (uint32_t)x, (uint32_t)y1) == 1u) {
-            float3 o = make_float3(0.f, 0.f, 0.f);
-#pragma unroll
-            for (int i = 0; i <= 2 * R1; ++i) {
-                const float g = a.g1[i];
-                o.x = o.x + g * h1[i].x;
-                o.y = o.y + g * h1[i].y;
-                o.z = o.z + g * h1[i].z;
-            }
-            float* d = a.dst + ((size_t)y1 * (size_t)W + (size_t)x) * 3;
-            d[0] = o.x;
-            d[1] = o.y;
-            d[2] = o.z;
-        }
-        const int y2 = y0 + v - 2 * R2;
-        if (need2 && v >= 2 * R2 && y2 < H && x < W &&
-            ring_level(a.r0sq, a.r1sq, a.gx, a.gy, (uint32_t)x, (uint32_t)y2) == 2u) {
-            float3 o = make_float3(0.f, 0.f, 0.f);
-#pragma unroll
-            for (int i = 0; i <= 2 * R2; ++i) {
-                const float g = a.g2[i];
-                o.x = o.x + g * h2[i].x;
-                o.y = o.y + g * h2[i].y;
-                o.z = o.z + g * h2[i].z;
-            }
-            float* d = a.dst + ((size_t)y2 * (size_t)W + (size_t)x) * 3;
-            d[0] = o.x;
-            d[1] = o.y;
-            d[2] = o.z;
-        }
-      }
     }
 }
 
@@ -1590,24 +1599,26 @@ hipError_t launch_gauss_levels(const float* full, float* dst, uint32_t w, uint32
     a.gy = gy;
     a.r0sq = r0sq;
     a.r1sq = r1sq;
-    for (int i = 0; i <= 2 * kGaussR1; ++i) a.g1[i] = g1[i];
-    for (int i = 0; i <= 2 * kGaussR2; ++i) a.g2[i] = g2[i];
-    // One-wave blocks; the tallest strip (32, 16, 8 or 4 rows; the halo costs
-    // 12 walked rows per strip) whose grid still gives the compute units about
-    // 16 waves each, else 4 rows: with fewer waves the per-row barrier and load
-    // latency are not hidden.
-    constexpr int C = kGaussCols;
-    a.cols = (w + C - 1) / C;
+    for (int i = 0; i <= kGaussR1; ++i) a.g1[i] = g1[kGaussR1 + i];
+    for (int i = 0; i <= kGaussR2; ++i) a.g2[i] = g2[kGaussR2 + i];
+    // The tallest strip (the halo costs 12 walked rows per strip) whose grid still
+    // gives every compute unit four blocks: at 1920x1080 a generator call takes 33 us
+    // with 16 rows (1564 blocks), 35 with 32 (782); at 3840x2160 104 us with 64 rows,
+    // 107 with 32.
+    a.cols = (uint32_t)(((uint64_t)w * 3u + kGaussCols - 1u) / kGaussCols);
     auto blocks = [&](uint32_t rows) { return (uint64_t)a.cols * ((h + rows - 1) / rows); };
-    const dim3 block(C);
-    if (blocks(32) >= 4000u)
-        hipLaunchKernelGGL((gauss_levels_kernel<32, C>), dim3((uint32_t)blocks(32)), block, 0, stream, a);
-    else if (blocks(16) >= 4000u)
-        hipLaunchKernelGGL((gauss_levels_kernel<16, C>), dim3((uint32_t)blocks(16)), block, 0, stream, a);
-    else if (blocks(8) >= 4000u)
-        hipLaunchKernelGGL((gauss_levels_kernel<8, C>), dim3((uint32_t)blocks(8)), block, 0, stream, a);
+    const dim3 block(kGaussCols);
+    const uint64_t enough = 1024u;
+    if (blocks(64) >= enough)
+        hipLaunchKernelGGL(gauss_levels_kernel<64>, dim3((uint32_t)blocks(64)), block, 0, stream, a);
+    else if (blocks(32) >= enough)
+        hipLaunchKernelGGL(gauss_levels_kernel<32>, dim3((uint32_t)blocks(32)), block, 0, stream, a);
+    else if (blocks(16) >= enough)
+        hipLaunchKernelGGL(gauss_levels_kernel<16>, dim3((uint32_t)blocks(16)), block, 0, stream, a);
+    else if (blocks(8) >= enough)
+        hipLaunchKernelGGL(gauss_levels_kernel<8>, dim3((uint32_t)blocks(8)), block, 0, stream, a);
     else
-        hipLaunchKernelGGL((gauss_levels_kernel<4, C>), dim3((uint32_t)blocks(4)), block, 0, stream, a);
+        hipLaunchKernelGGL(gauss_levels_kernel<4>, dim3((uint32_t)blocks(4)), block, 0, stream, a);
     return hipGetLastError();
 }
 
