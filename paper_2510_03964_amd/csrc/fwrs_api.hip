@@ -775,7 +775,8 @@ template <typename TileFn>
 int layout_tick(const fwrs_frame* frames, int n, bool reverse, TileFn tile, TickWork w, fwrs::TickHead* head,
                 FrameDesc* descs, int* ops, int& kind)
 {
-    kind = fwrs::kTickAlone;
+    int groups_kind = fwrs::kTickAlone;
+    bool per_slot = false;
     const uint64_t mark = g_tick_marks.fetch_add(1u, std::memory_order_relaxed) + 1u;
     int groups = 0;
     for (int i = 0; i < n; ++i) {
@@ -817,8 +818,9 @@ int layout_tick(const fwrs_frame* frames, int n, bool reverse, TileFn tile, Tick
         const int op = nf > 1 && w.tame[g] != 0 && group_kernel(x) ? fwrs::kOpGroup : fused_op_at(x, d.t, plane);
         w.plane[g] = (plane_after(x, op) ? 1 : 0) | (tame ? 2 : 0);
         d.tame = tame ? 1u : 0u;
-        if (nf > 1 && kind != fwrs::kTickGroups8)
-            kind = op == fwrs::kOpGroup && x->k == 8 ? fwrs::kTickGroups8 : fwrs::kTickGroups;
+        if (nf > 1 && groups_kind != fwrs::kTickGroups8)
+            groups_kind = op == fwrs::kOpGroup && x->k == 8 ? fwrs::kTickGroups8 : fwrs::kTickGroups;
+        per_slot = per_slot || fwrs::per_slot_mode(x->prm.bias_mode);
         ops[i] = op;
         d.op = (uint32_t)op;
         d.res_ok = plane ? 1u : 0u;
@@ -826,6 +828,7 @@ int layout_tick(const fwrs_frame* frames, int n, bool reverse, TileFn tile, Tick
         d.nf = at == 0 ? (uint32_t)nf : 1u;
         d.more = at == 0 ? (uint32_t)w.base[g] : 0u;
     }
+    kind = groups_kind + (per_slot ? fwrs::kTickPerSlot : 0);
     head->n = (uint32_t)groups;
     head->total = 0;
     head->pad0 = head->pad1 = 0;

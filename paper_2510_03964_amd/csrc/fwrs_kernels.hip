@@ -345,143 +345,6 @@ __device__ __forceinline__ void pixel_group(const FrameDesc& d0, const FrameDesc
 }
 
 // ---------------------------------------------------------------------------
-// One pixel under a per-slot mode, one value per slot in wslot[p * k + j]:
-//  - Eq. 7 (FULL): the slot's own w_sum, biased by the slot's colour
-//    difference to the new pixel before its Alg. 2 decision;
-//  - A-ES: the log2 key of the slot's sample; the candidate's key log2(u) / w
-//    replaces it when larger (Sec. 3.1).
-// Needs the new colour for every pixel and every slot's record, so the records
-// are read by every op that updates.  Same store layout otherwise.
-// ---------------------------------------------------------------------------
-template <int SLOTS, int OP, bool FOV = false>
-__device__ __forceinline__ uint32_t pixel_per_slot(const FrameDesc& d, uint32_t x, uint32_t y,
-                                                   const FovSrc* fs = nullptr)
-{
-    const uint32_t p = y * d.width + x;
-    constexpr bool kTame = SLOTS != kWild;
-    constexpr int K = SLOTS > 0 ? SLOTS : 0;
-    const int kk = K ? K : (int)d.k;
-    constexpr int R = K ? K : 1;
-    constexpr bool kUpdates = OP == kPush || OP == kFused || OP == kIncremental;
-    constexpr bool kResolves = OP == kFused || OP == kIncremental;
-    float4* rec = reinterpret_cast<float4*>(d.rec) + (size_t)p * (size_t)kk;
-    uint32_t* idx = d.idx + (size_t)p * (size_t)kk;
-    float* wslot = d.wsum + (size_t)p * (size_t)kk;
-
-    // every slot's record and sum up front (K > 0), then the pixel's own inputs
-    float4 r[R];
-    float W[R];
-    if (K) {
-#pragma unroll
-        for (int j = 0; j < R; ++j) r[j] = ld4<kNtRecLd>(rec + j);
-        if (K % 4 == 0) {
-#pragma unroll
-            for (int j = 0; j < R; j += 4) {
-                const float4 v = ld4<kNtWsumLd>(reinterpret_cast<const float4*>(wslot + j));
-                W[j] = v.x;
-                W[(j + 1) % R] = v.y;
-                W[(j + 2) % R] = v.z;
-                W[(j + 3) % R] = v.w;
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < R; ++j) W[j] = ld<kNtWsumLd>(wslot + j);
-        }
-    }
-    uint32_t lv;
-    float c0, c1, c2;
-    if constexpr (FOV) {
-        lv = fov_level(*fs, d.gx, d.gy, x, y);
-        const float3 c = fov_colour(*fs, x, y, p, lv);
-        c0 = c.x;
-        c1 = c.y;
-        c2 = c.z;
-    } else {
-        lv = ld<kNtLevel>(d.level + p);
-        const float* color = d.color + 3 * (size_t)p;
-        c0 = ld<kNtColor>(color + 0);
-        c1 = ld<kNtColor>(color + 1);
-        c2 = ld<kNtColor>(color + 2);
-    }
-    const float dx = ((float)x + 0.5f) - d.gx;
-    const float dy = ((float)y + 0.5f) - d.gy;
-    const float w = weight_eq4<kTame>(d.c, dx * dx + dy * dy, lv);
-    const bool aes = d.bias == kAes;
-    // Eq. 7: a slot whose sample has the new pixel's colour has |dL| = 0 exactly
-    // (same_colour), so its Lab and CIE94 are not evaluated, nor the new
-    // pixel's Lab when that holds for every slot.
-    const bool bounded = lab_bounded(c0, c1, c2);
-    uint32_t same = 0u;
-    if (K && !aes) {
-#pragma unroll
-        for (int j = 0; j < R; ++j)
-            if (bounded && same_colour(r[j], c0, c1, c2)) same |= 1u << j;
-    }
-    float3 lab_new = make_float3(0.f, 0.f, 0.f);
-    if (!aes && (!K || same != (1u << R) - 1u)) lab_new = rgb_to_lab(c0, c1, c2);
-    const float4 fresh = make_float4(w, c0, c1, c2);
-
-    float S = 0.f, a0 = 0.f, a1 = 0.f, a2 = 0.f;
-    uint32_t tk = 0u;
-    uint4 words = make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-    for (int j = 0; j < kk; ++j) {
-        float4 v = K ? r[K ? j : 0] : ld4<kNtRecLd>(rec + j);
-        const float W1 = K ? W[K ? j : 0] : ld<kNtWsumLd>(wslot + j);
-        if ((j & 3) == 0) words = philox4x32_10(p, d.t, (uint32_t)(j >> 2), d.seed, d.stream_id);
-        const uint32_t word = (j & 3) == 0 ? words.x : (j & 3) == 1 ? words.y : (j & 3) == 2 ? words.z : words.w;
-        bool take;
-        float s;
-        if (aes) {
-            // A-ES: the larger key log2(u) / w wins; the slot keeps its sample's key
-            const float kn = log2_unit(word) / w;
-            take = kn > W1;
-            s = take ? kn : W1;
-        } else {
-            // Eq. 7 against this slot's sample, then the slot's Alg. 2 decision
-            const bool same_j = K ? ((same >> j) & 1u) != 0u : bounded && same_colour(v, c0, c1, c2);
-            float dl = 0.0f;
-            if (!same_j) dl = delta_l(v.y, v.z, v.w, lab_new);
-            const float W1b = bias_eq7<kTame>(W1, w, dl);
-            s = W1b + w;
-            take = takes<kTame>(word, s, W1b);
-        }
-        if (take) {
-            tk |= 1u << j;
-            v = fresh;
-            st4<kNtRecSt>(rec + j, fresh);
-            st<kNtIdxSt>(idx + j, d.t);
-        }
-        if (K) W[K ? j : 0] = s;
-        else st<kNtWsumSt>(wslot + j, s);
-        S = S + v.x;
-        a0 = a0 + v.x * v.y;
-        a1 = a1 + v.x * v.z;
-        a2 = a2 + v.x * v.w;
-    }
-    if (K) {
-        if (K % 4 == 0) {
-#pragma unroll
-            for (int j = 0; j < R; j += 4)
-                st4<kNtWsumSt>(reinterpret_cast<float4*>(wslot + j),
-                               make_float4(W[j], W[(j + 1) % R], W[(j + 2) % R], W[(j + 3) % R]));
-        } else {
-#pragma unroll
-            for (int j = 0; j < R; ++j) st<kNtWsumSt>(wslot + j, W[j]);
-        }
-    }
-    if (kResolves && (OP != kIncremental || tk)) {
-        const float rs = resolve_scale<kTame>(S);
-        float* o = d.out + 3 * (size_t)p;
-        st<kNtOut>(o + 0, a0 * rs);
-        st<kNtOut>(o + 1, a1 * rs);
-        st<kNtOut>(o + 2, a2 * rs);
-    }
-    static_assert(kUpdates, "the resolve-only pass is the same under every bias mode");
-    return __popc(tk) + (tk ? 0x10000u : 0u);
-}
-
-// ---------------------------------------------------------------------------
 // One work item (256 pixels).  The wave index is made explicit as a uniform
 // value so the tile arithmetic runs on the scalar unit.
 // ---------------------------------------------------------------------------
@@ -829,6 +692,294 @@ __device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t it
     return slots + (changed << 16);
 }
 
+// ---------------------------------------------------------------------------
+// A frame of a per-slot mode, one value per slot in wsum[p * k + j]:
+//  - Eq. 7 (FULL): the slot's own w_sum, biased by the slot's colour
+//    difference to the new pixel before its Alg. 2 decision;
+//  - A-ES: the log2 key of the slot's sample; the candidate's key log2(u) / w
+//    replaces it when larger (Sec. 3.1).
+// Every slot's record and value are read by every op that updates, so the wave
+// goes through its 64 pixels with one lane per slot: the pixel's weight, colour
+// and Philox words are computed with one lane per pixel and handed over in LDS,
+// records and values are coalesced accesses, a round's being loaded while the
+// one before is worked on, and Lab and CIE94 run only in the rounds (16 pixels at
+// k = 4) that hold a slot whose colour differs.  The resolve goes back through
+// LDS to leave by rows.  Against one lane per pixel streaming its record slot by
+// slot, as ticks and slot counts other than 4 and 8 had it: four 900x600 Eq. 7
+// sessions in a tick 82.4 -> 44.5 us, five 700x500 A-ES k = 8 sessions 170 -> 54,
+// 1600x1000 Eq. 7 k = 3 49 -> 39, k = 1 21.2 -> 15.4.
+// ---------------------------------------------------------------------------
+// Whether a frame's store is larger than the 256 MB Infinity Cache (20 bytes per
+// slot and a value): its records are then read non-temporally, which leaves the
+// cache to the partial lines that replaced slots write (2560x1440 Eq. 7, k = 4,
+// three sessions in turn: 99.8 -> 89.9 us; a store that fits: 800x600 16.4 ->
+// 17.7), and at k = 4 and 8 smaller stores take one lane per pixel (800x600 14.8
+// us against 16.4; 1600x1000 A-ES k = 4 31 either way).
+inline bool store_streams(const FrameDesc& d)
+{
+    return (uint64_t)d.width * d.height * d.k * 24u > (256ull << 20);
+}
+
+__device__ __forceinline__ float4 ld4_streamed(const float4* p)
+{
+    const v4f v = __builtin_nontemporal_load(gbl(reinterpret_cast<const v4f*>(p)));
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+
+template <int SLOTS>
+struct PerSlotShare {                           // one wave's pixels
+    static constexpr int kBlocks = SLOTS > 0 ? (SLOTS + 3) / 4 : (kMaxK + 3) / 4;
+    uint2 pixel[64];                            // {p, inside}
+    float4 colour[64];                          // the new colour, weight; then the resolve, changed
+    uint32_t words[64][4 * kBlocks];            // Philox words, one per slot
+};
+
+template <int SLOTS, int OP, bool FOV = false, bool STREAMED = false>
+__device__ __forceinline__ uint32_t per_slot_tile(const FrameDesc& d, uint32_t item, uint32_t wave,
+                                                  PerSlotShare<SLOTS>& sh, const FovSrc* fs = nullptr)
+{
+    static_assert(OP == kPush || OP == kFused || OP == kIncremental, "the resolve-only pass is the same under every mode");
+    constexpr bool kTame = SLOTS != kWild;
+    constexpr int K = SLOTS > 0 ? SLOTS : 0;
+    constexpr bool kResolves = OP != kPush;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t kk = K ? (uint32_t)K : d.k;
+    const uint32_t lg = group_log2<K>(kk), first = group_first<K>(kk);
+    const uint32_t j = lane & ((1u << lg) - 1u), per = 64u >> lg;
+    const bool slot = K || j < kk;
+    const bool aes = d.bias == kAes;
+    constexpr uint32_t D = K == 4 ? 4u : 1u;      // rounds loaded ahead
+
+    // 1. one lane per pixel
+    uint32_t x, y;
+    const bool in = item_pixel_of(d, item, wave, lane, x, y);
+    if (!in) x = y = 0u;                        // lanes outside read pixel 0 and store nothing
+    const uint32_t p = y * d.width + x;
+    sh.pixel[lane] = make_uint2(p, in ? 1u : 0u);
+    uint32_t lv;
+    float c0, c1, c2;
+    if constexpr (FOV) {
+        lv = fov_level(*fs, d.gx, d.gy, x, y);
+        const float3 c = fov_colour(*fs, x, y, p, lv);
+        c0 = c.x;
+        c1 = c.y;
+        c2 = c.z;
+    } else {
+        lv = ld<kNtLevel>(d.level + p);
+        const float* color = d.color + 3 * (size_t)p;
+        c0 = ld<kNtColor>(color + 0);
+        c1 = ld<kNtColor>(color + 1);
+        c2 = ld<kNtColor>(color + 2);
+    }
+    wave_lds_fence();
+
+    // the records and values of the first rounds, in flight over the pixels' arithmetic
+    float4 v[D];
+    float W1[D];
+    auto load = [&](uint32_t b, float4& rec, float& val) {
+        const uint32_t q = sh.pixel[b + (lane >> lg)].x;
+        const size_t at = (size_t)q * kk + (slot ? j : 0u);
+        const float4* from = reinterpret_cast<const float4*>(d.rec) + at;
+        if constexpr (STREAMED) rec = ld4_streamed(from);
+        else rec = ld4<kNtRecLd>(from);
+        val = ld<kNtWsumLd>(d.wsum + at);
+    };
+#pragma unroll
+    for (uint32_t q = 0; q < D; ++q)
+        if (q * per < 64u) load(q * per, v[q], W1[q]);
+
+    for (uint32_t b = 0; 4u * b < kk; ++b) {
+        const uint4 r = philox4x32_10(p, d.t, b, d.seed, d.stream_id);
+        *reinterpret_cast<uint4*>(&sh.words[lane][4u * b]) = r;
+    }
+    {
+        const float dx = ((float)x + 0.5f) - d.gx;
+        const float dy = ((float)y + 0.5f) - d.gy;
+        sh.colour[lane] = make_float4(c0, c1, c2, weight_eq4<kTame>(d.c, dx * dx + dy * dy, lv));
+    }
+    wave_lds_fence();
+
+    // 2. one lane per slot
+    uint32_t slots = 0u, changed = 0u;
+    for (uint32_t b0 = 0; b0 < 64u; b0 += D * per)
+#pragma unroll
+    for (uint32_t q = 0; q < D; ++q) {
+        const uint32_t b = b0 + q * per;
+        if (b >= 64u) break;
+        const uint32_t e = b + (lane >> lg);
+        const uint2 now = sh.pixel[e];
+        const size_t s_at = (size_t)now.x * kk + (slot ? j : 0u);
+        float4 r = v[q];
+        const float Wj = W1[q];
+        if (b + D * per < 64u) load(b + D * per, v[q], W1[q]);
+        const float4 c = sh.colour[e];
+        const float w = c.w;
+        const uint32_t word = sh.words[e][slot ? j : 0u];
+        bool take;
+        float s;
+        if (aes) {
+            // A-ES: the larger key log2(u) / w wins; the slot keeps its sample's key
+            const float kn = kTame ? div_rn(log2_unit(word), w) : log2_unit(word) / w;
+            take = kn > Wj;
+            s = take ? kn : Wj;
+        } else {
+            // Eq. 7 against this slot's sample, then the slot's Alg. 2 decision.  A
+            // sample with the new pixel's colour has |dL| = 0 exactly (same_colour):
+            // its Lab and CIE94 are not evaluated.
+            float dl = 0.0f;
+            if (!(lab_bounded(c.x, c.y, c.z) && same_colour(r, c.x, c.y, c.z)))
+                dl = delta_l(r.y, r.z, r.w, rgb_to_lab(c.x, c.y, c.z));
+            const float W1b = bias_eq7<kTame>(Wj, w, dl);
+            s = W1b + w;
+            take = takes<kTame>(word, s, W1b);
+        }
+        const bool own = slot && now.y != 0u;
+        take = take && own;
+        if (take) r = make_float4(w, c.x, c.y, c.z);
+        const uint64_t took = __ballot(take);
+        slots += (uint32_t)__builtin_popcountll(took);
+        const bool any = ((took >> (lane & ~((1u << lg) - 1u))) & ((1ull << (1u << lg)) - 1ull)) != 0u;
+        changed += (uint32_t)__builtin_popcountll(__ballot(any && j == 0u));
+        float q0 = 0.f, q1 = 0.f, q2 = 0.f;
+        if constexpr (kResolves) {
+            const float rs = resolve_scale<kTame>(group_sum<K>(r.x, kk));
+            q0 = group_sum<K>(r.x * r.y, kk) * rs;
+            q1 = group_sum<K>(r.x * r.z, kk) * rs;
+            q2 = group_sum<K>(r.x * r.w, kk) * rs;
+        }
+        if (own) st<kNtWsumSt>(d.wsum + s_at, s);
+        if (take) {
+            st4<kNtRecSt>(reinterpret_cast<float4*>(d.rec) + s_at, r);
+            st<kNtIdxSt>(d.idx + s_at, d.t);
+        }
+        if (kResolves && j == first) sh.colour[e] = make_float4(q0, q1, q2, any ? 1.f : 0.f);
+    }
+    wave_lds_fence();
+
+    // 3. one lane per pixel: the output rows
+    if constexpr (kResolves) {
+        const float4 q = sh.colour[lane];
+        if (in && (OP != kIncremental || q.w != 0.f)) {
+            float* o = d.out + 3 * (size_t)p;
+            st<OP == kIncremental ? 0u : kNtOut>(o + 0, q.x);
+            st<OP == kIncremental ? 0u : kNtOut>(o + 1, q.y);
+            st<OP == kIncremental ? 0u : kNtOut>(o + 2, q.z);
+        }
+    }
+    return slots + (changed << 16);
+}
+
+// The same with one lane per pixel, the record and values in registers: fewer
+// instructions per pixel, which counts where the store stays in the Infinity
+// Cache (store_streams).
+template <int K, int OP, bool FOV = false>
+__device__ __forceinline__ uint32_t pixel_per_slot(const FrameDesc& d, uint32_t x, uint32_t y,
+                                                   const FovSrc* fs = nullptr)
+{
+    const uint32_t p = y * d.width + x;
+    static_assert(K > 0 && K % 4 == 0, "whole Philox blocks, 16-byte groups of values");
+    constexpr bool kUpdates = OP == kPush || OP == kFused || OP == kIncremental;
+    constexpr bool kResolves = OP == kFused || OP == kIncremental;
+    float4* rec = reinterpret_cast<float4*>(d.rec) + (size_t)p * K;
+    uint32_t* idx = d.idx + (size_t)p * K;
+    float* wslot = d.wsum + (size_t)p * K;
+
+    // every slot's record and sum up front, then the pixel's own inputs
+    float4 r[K];
+    float W[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) r[j] = ld4<kNtRecLd>(rec + j);
+#pragma unroll
+    for (int j = 0; j < K; j += 4) {
+        const float4 v = ld4<kNtWsumLd>(reinterpret_cast<const float4*>(wslot + j));
+        W[j] = v.x;
+        W[j + 1] = v.y;
+        W[j + 2] = v.z;
+        W[j + 3] = v.w;
+    }
+    uint32_t lv;
+    float c0, c1, c2;
+    if constexpr (FOV) {
+        lv = fov_level(*fs, d.gx, d.gy, x, y);
+        const float3 c = fov_colour(*fs, x, y, p, lv);
+        c0 = c.x;
+        c1 = c.y;
+        c2 = c.z;
+    } else {
+        lv = ld<kNtLevel>(d.level + p);
+        const float* color = d.color + 3 * (size_t)p;
+        c0 = ld<kNtColor>(color + 0);
+        c1 = ld<kNtColor>(color + 1);
+        c2 = ld<kNtColor>(color + 2);
+    }
+    const float dx = ((float)x + 0.5f) - d.gx;
+    const float dy = ((float)y + 0.5f) - d.gy;
+    const float w = weight_eq4<true>(d.c, dx * dx + dy * dy, lv);
+    const bool aes = d.bias == kAes;
+    // Eq. 7: a slot whose sample has the new pixel's colour has |dL| = 0 exactly
+    // (same_colour), so its Lab and CIE94 are not evaluated, nor the new
+    // pixel's Lab when that holds for every slot.
+    const bool bounded = lab_bounded(c0, c1, c2);
+    uint32_t same = 0u;
+    if (!aes) {
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+            if (bounded && same_colour(r[j], c0, c1, c2)) same |= 1u << j;
+    }
+    float3 lab_new = make_float3(0.f, 0.f, 0.f);
+    if (!aes && same != (1u << K) - 1u) lab_new = rgb_to_lab(c0, c1, c2);
+    const float4 fresh = make_float4(w, c0, c1, c2);
+
+    float S = 0.f, a0 = 0.f, a1 = 0.f, a2 = 0.f;
+    uint32_t tk = 0u;
+    uint4 words = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        float4 v = r[j];
+        const float W1 = W[j];
+        if ((j & 3) == 0) words = philox4x32_10(p, d.t, (uint32_t)(j >> 2), d.seed, d.stream_id);
+        const uint32_t word = (j & 3) == 0 ? words.x : (j & 3) == 1 ? words.y : (j & 3) == 2 ? words.z : words.w;
+        bool take;
+        float s;
+        if (aes) {
+            // A-ES: the larger key log2(u) / w wins; the slot keeps its sample's key
+            const float kn = div_rn(log2_unit(word), w);
+            take = kn > W1;
+            s = take ? kn : W1;
+        } else {
+            // Eq. 7 against this slot's sample, then the slot's Alg. 2 decision
+            float dl = 0.0f;
+            if (((same >> j) & 1u) == 0u) dl = delta_l(v.y, v.z, v.w, lab_new);
+            const float W1b = bias_eq7<true>(W1, w, dl);
+            s = W1b + w;
+            take = takes<true>(word, s, W1b);
+        }
+        if (take) {
+            tk |= 1u << j;
+            v = fresh;
+            st4<kNtRecSt>(rec + j, fresh);
+            st<kNtIdxSt>(idx + j, d.t);
+        }
+        W[j] = s;
+        S = S + v.x;
+        a0 = a0 + v.x * v.y;
+        a1 = a1 + v.x * v.z;
+        a2 = a2 + v.x * v.w;
+    }
+#pragma unroll
+    for (int j = 0; j < K; j += 4)
+        st4<kNtWsumSt>(reinterpret_cast<float4*>(wslot + j), make_float4(W[j], W[j + 1], W[j + 2], W[j + 3]));
+    if (kResolves && (OP != kIncremental || tk)) {
+        const float rs = resolve_scale<true>(S);
+        float* o = d.out + 3 * (size_t)p;
+        st<kNtOut>(o + 0, a0 * rs);
+        st<kNtOut>(o + 1, a1 * rs);
+        st<kNtOut>(o + 2, a2 * rs);
+    }
+    static_assert(kUpdates, "the resolve-only pass is the same under every bias mode");
+    return __popc(tk) + (tk ? 0x10000u : 0u);
+}
+
 // Work items are visited in reverse order on odd frames, so each frame starts
 // where the previous one ended: the store it touched last is still in the
 // 256 MB Infinity Cache (a third of a 4K, k = 4 store) when it is read again.
@@ -838,27 +989,32 @@ __device__ __forceinline__ uint32_t frame_item(uint32_t block, uint32_t items, u
     return (t & 1u) ? items - 1u - block : block;
 }
 
-// Work items [T block, T block + T) of a frame (per-slot modes: T = 1).
+// Work items [T block, T block + T) of a frame.  Per-slot modes, an item per block:
+// T = 0 one lane per pixel, 1 one lane per slot, 2 the same with streamed records.
 template <int K, int OP, bool PER_SLOT, int T, bool FOV>
 __device__ __forceinline__ void frame_block(const FrameDesc& d, uint32_t block, const FovSrc* fs)
 {
-    if constexpr (PER_SLOT) {
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if constexpr (PER_SLOT && T == 0) {
         uint32_t x, y, n = 0u;
-        if (item_pixel(d, block, x, y)) n = pixel_per_slot<K, OP, FOV>(d, x, y, fs);
+        if (item_pixel_of(d, block, wave, threadIdx.x & 63u, x, y)) n = pixel_per_slot<K, OP, FOV>(d, x, y, fs);
         if (d.stats) add_stats(d.stats, n);
+    } else if constexpr (PER_SLOT) {
+        __shared__ PerSlotShare<K> share[kBlock / 64];
+        const uint32_t n = per_slot_tile<K, OP, FOV, T == 2>(d, block, wave, share[wave], fs);
+        if (d.stats) add_stats_uniform(d.stats, n);
     } else {
         __shared__ uint4 list[kBlock / 64][64 * T];
-        const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const uint32_t n = stream_tiles<K, OP, T, FOV>(d, T * block, wave, list[wave], fs);
         if (OP != kResolve && d.stats) add_stats_uniform(d.stats, n);
     }
 }
 
-// Waves per SIMD the frame kernels are compiled for (per-slot modes: no bound).
-constexpr int frame_waves(bool per_slot) { return per_slot ? 1 : 8; }
+// Waves per SIMD the frame kernels are compiled for (T = 0: no bound).
+constexpr int kFrameWaves = 8;
 
 template <int K, int OP, bool PER_SLOT = false, int T = 1>
-__global__ __launch_bounds__(kBlock, frame_waves(PER_SLOT)) void frame_kernel(FrameDesc d)
+__global__ __launch_bounds__(kBlock, T ? kFrameWaves : 1) void frame_kernel(FrameDesc d)
 {
     frame_block<K, OP, PER_SLOT, T, false>(d, frame_item(blockIdx.x, gridDim.x, d.t), nullptr);
 }
@@ -884,16 +1040,38 @@ __global__ __launch_bounds__(kBlock, frame_waves(PER_SLOT)) void frame_kernel(Fr
 // frames in turn through the store, every pixel in the same thread, so each
 // frame reads what the one before wrote.
 // ---------------------------------------------------------------------------
+// A wave's LDS in the batched kernel: a list (stream_tiles), in ticks with
+// per-slot modes (PS) also a share (per_slot_tile).
+template <bool PS>
+union TickShare {
+    uint4 list[64];
+};
+template <>
+union TickShare<true> {
+    uint4 list[64];
+    PerSlotShare<0> slots;
+    PerSlotShare<1> slots1;
+    PerSlotShare<2> slots2;
+    PerSlotShare<4> slots4;
+    PerSlotShare<kWild> wild;
+};
+
 // One wave's share of a lone frame's work item; counts its replaced slots and
 // changed pixels.
-__device__ __forceinline__ void tick_item(const FrameDesc& d, uint32_t local, uint32_t wave, uint4* list)
+template <bool PS>
+__device__ __forceinline__ void tick_item(const FrameDesc& d, uint32_t local, uint32_t wave, TickShare<PS>& sh)
 {
-    if (per_slot_mode(d.bias)) {
-        uint32_t x, y, n = 0u;
-        if (item_pixel_of(d, local, wave, threadIdx.x & 63u, x, y))
-            n = d.tame ? pixel_per_slot<0, kFused>(d, x, y) : pixel_per_slot<kWild, kFused>(d, x, y);
-        if (d.stats) add_stats(d.stats, n);
-        return;
+    uint4* list = sh.list;
+    if constexpr (PS) {
+        if (per_slot_mode(d.bias)) {
+            const uint32_t n = !d.tame     ? per_slot_tile<kWild, kFused>(d, local, wave, sh.wild)
+                               : d.k == 1u ? per_slot_tile<1, kFused>(d, local, wave, sh.slots1)
+                               : d.k == 2u ? per_slot_tile<2, kFused>(d, local, wave, sh.slots2)
+                               : d.k == 4u ? per_slot_tile<4, kFused>(d, local, wave, sh.slots4)
+                                           : per_slot_tile<0, kFused>(d, local, wave, sh.slots);
+            if (d.stats) add_stats_uniform(d.stats, n);
+            return;
+        }
     }
     uint32_t n = 0u;
 #define FWRS_TICK_OPS(KK)                                                        \
@@ -915,10 +1093,10 @@ __device__ __forceinline__ void tick_item(const FrameDesc& d, uint32_t local, ui
     if (d.stats) add_stats_uniform(d.stats, n);
 }
 
-// One work item of a group of d.nf > 1 frames (d its leader); G as tick_kernel's.
-template <int G>
+// One work item of a group of d.nf > 1 frames (d its leader); G, PS as tick_blocks'.
+template <int G, bool PS>
 __device__ __forceinline__ void tick_group_item(const FrameDesc& d, const FrameDesc* __restrict__ descs,
-                                                uint32_t local, uint32_t wave, uint4* list)
+                                                uint32_t local, uint32_t wave, TickShare<PS>& sh)
 {
     const FrameDesc* later = descs + d.more;
     if (d.op == kGroup) {
@@ -938,19 +1116,21 @@ __device__ __forceinline__ void tick_group_item(const FrameDesc& d, const FrameD
     }
     for (uint32_t f = 0; f < d.nf; ++f) {
         const FrameDesc& df = f == 0u ? d : later[f - 1u];
-        tick_item(df, local, wave, list);
+        tick_item<PS>(df, local, wave, sh);
     }
 }
 
-// The tick of table (head, descs), block by block; G: what the tick holds
-// (kTickAlone: no groups; kTickGroups: groups, none run as kGroup with k = 8;
-// kTickGroups8: some are).  A group holds its pixels' whole records across
+// The tick of table (head, descs), block by block; KIND: what the tick holds
+// (G = kTickAlone: no groups; kTickGroups: groups, none run as kGroup with k = 8;
+// kTickGroups8: some are; PS, + kTickPerSlot: frames of per-slot modes).  A group holds its pixels' whole records across
 // its frames, which takes more registers than the single-frame paths (at k = 8
 // far more), so each kind of tick runs the instantiation with only the paths
 // it needs, at the best occupancy they allow.
-template <int G>
+template <int KIND>
 __device__ __forceinline__ void tick_blocks(const TickHead& head, const FrameDesc* __restrict__ descs)
 {
+    constexpr int G = KIND % kTickPerSlot;
+    constexpr bool PS = KIND >= kTickPerSlot;
     const uint32_t item = blockIdx.x;
     if (item >= head.total) return;
     uint32_t f = 0u, hi = head.n - 1u;               // last leader whose first item <= item
@@ -963,13 +1143,16 @@ __device__ __forceinline__ void tick_blocks(const TickHead& head, const FrameDes
     uint32_t local = item - d.first;
     if (d.rev) local = d.items - 1u - local;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    __shared__ uint4 list[kBlock / 64][64];
-    if (G != kTickAlone && d.nf > 1u) tick_group_item<G>(d, descs, local, wave, list[wave]);
-    else tick_item(d, local, wave, list[wave]);
+    __shared__ TickShare<PS> share[kBlock / 64];
+    if (G != kTickAlone && d.nf > 1u) tick_group_item<G, PS>(d, descs, local, wave, share[wave]);
+    else tick_item<PS>(d, local, wave, share[wave]);
 }
 
 // Waves per SIMD the kernels are compiled for.
-constexpr int tick_waves(int kind) { return kind == kTickGroups8 ? 5 : kind == kTickGroups ? 7 : 8; }
+constexpr int tick_waves(int kind)
+{
+    return kind % kTickPerSlot == kTickGroups8 ? 5 : kind == kTickAlone ? 8 : kind == kTickGroups ? 7 : 6;
+}
 
 // The table in device memory.
 template <int G>
@@ -1125,7 +1308,7 @@ __device__ __forceinline__ uint32_t pixel_reproject(const ReprojDesc& r, uint32_
         float W1j = W1b, sj = s;
         bool take;
         if (PER_SLOT && aes) {
-            const float kn = log2_unit(word) / w;
+            const float kn = kTame ? div_rn(log2_unit(word), w) : log2_unit(word) / w;
             take = kn > Wj;
             st<kNtWsumSt>(d.wsum + (size_t)p * (size_t)kk + j, take ? kn : Wj);
         } else {
@@ -1464,10 +1647,10 @@ __global__ __launch_bounds__(kBlock) void foveate_kernel(FoveateArgs a)
     a.level[p] = (uint8_t)lv;
 }
 
-template <int K, bool PER_SLOT, int OP>
-__global__ __launch_bounds__(kBlock, frame_waves(PER_SLOT)) void foveated_kernel(FovDesc fd)
+template <int K, bool PER_SLOT, int OP, int T = 1>
+__global__ __launch_bounds__(kBlock, T ? kFrameWaves : 1) void foveated_kernel(FovDesc fd)
 {
-    frame_block<K, OP, PER_SLOT, 1, true>(fd.f, frame_item(blockIdx.x, gridDim.x, fd.f.t), &fd.s);
+    frame_block<K, OP, PER_SLOT, T, true>(fd.f, frame_item(blockIdx.x, gridDim.x, fd.f.t), &fd.s);
 }
 
 __global__ void fill_u32_kernel(uint32_t* __restrict__ p, size_t n, uint32_t v)
@@ -1497,6 +1680,20 @@ static hipError_t launch_shared(const FrameDesc& d, hipStream_t stream)
     return hipGetLastError();
 }
 
+template <int OP, int T>
+static void launch_per_slot(const FrameDesc& d, hipStream_t stream)
+{
+    const dim3 grid(d.items), block(kBlock);
+    switch (slots_arg(d)) {
+        case kWild: hipLaunchKernelGGL((frame_kernel<kWild, OP, true, T>), grid, block, 0, stream, d); break;
+        case 1: hipLaunchKernelGGL((frame_kernel<1, OP, true, T>), grid, block, 0, stream, d); break;
+        case 2: hipLaunchKernelGGL((frame_kernel<2, OP, true, T>), grid, block, 0, stream, d); break;
+        case 4: hipLaunchKernelGGL((frame_kernel<4, OP, true, T>), grid, block, 0, stream, d); break;
+        case 8: hipLaunchKernelGGL((frame_kernel<8, OP, true, T>), grid, block, 0, stream, d); break;
+        default: hipLaunchKernelGGL((frame_kernel<0, OP, true, T>), grid, block, 0, stream, d); break;
+    }
+}
+
 template <int OP>
 static hipError_t launch_frame_op(const FrameDesc& d, hipStream_t stream)
 {
@@ -1504,12 +1701,10 @@ static hipError_t launch_frame_op(const FrameDesc& d, hipStream_t stream)
     if constexpr (OP == kPush || OP == kFused || OP == kIncremental) {
         if (per_slot_mode(d.bias)) {
             const dim3 grid(d.items), block(kBlock);
-            switch (slots_arg(d)) {
-                case kWild: hipLaunchKernelGGL((frame_kernel<kWild, OP, true>), grid, block, 0, stream, d); break;
-                case 4: hipLaunchKernelGGL((frame_kernel<4, OP, true>), grid, block, 0, stream, d); break;
-                case 8: hipLaunchKernelGGL((frame_kernel<8, OP, true>), grid, block, 0, stream, d); break;
-                default: hipLaunchKernelGGL((frame_kernel<0, OP, true>), grid, block, 0, stream, d); break;
-            }
+            if (store_streams(d)) launch_per_slot<OP, 2>(d, stream);
+            else if (d.tame && d.k == 4u) hipLaunchKernelGGL((frame_kernel<4, OP, true, 0>), grid, block, 0, stream, d);
+            else if (d.tame && d.k == 8u) hipLaunchKernelGGL((frame_kernel<8, OP, true, 0>), grid, block, 0, stream, d);
+            else launch_per_slot<OP, 1>(d, stream);
             return hipGetLastError();
         }
     }
@@ -1532,17 +1727,19 @@ hipError_t launch_frame(const FrameDesc& d, int op, hipStream_t stream)
     }
 }
 
+// One of a table of kernels, one per kind of tick.
+#define FWRS_TICK_KINDS(f) {f<0>, f<1>, f<2>, f<3>, f<4>, f<5>}
+static_assert(kTickKinds == 6, "a kernel per kind");
+static void (*const kTickKernels[])(const TickHead*, const FrameDesc*) = FWRS_TICK_KINDS(tick_kernel);
+static void (*const kTickArgsKernels[])(TickArgs) = FWRS_TICK_KINDS(tick_args_kernel);
+#undef FWRS_TICK_KINDS
+
 hipError_t launch_tick(const void* table, uint32_t grid, int kind, hipStream_t stream)
 {
     if (grid == 0u) return hipSuccess;
     const TickHead* head = static_cast<const TickHead*>(table);
     const FrameDesc* descs = reinterpret_cast<const FrameDesc*>(static_cast<const char*>(table) + kTickDescOffset);
-    if (kind == kTickGroups8)
-        hipLaunchKernelGGL(tick_kernel<kTickGroups8>, dim3(grid), dim3(kBlock), 0, stream, head, descs);
-    else if (kind == kTickGroups)
-        hipLaunchKernelGGL(tick_kernel<kTickGroups>, dim3(grid), dim3(kBlock), 0, stream, head, descs);
-    else
-        hipLaunchKernelGGL(tick_kernel<kTickAlone>, dim3(grid), dim3(kBlock), 0, stream, head, descs);
+    hipLaunchKernelGGL(kTickKernels[kind], dim3(grid), dim3(kBlock), 0, stream, head, descs);
     return hipGetLastError();
 }
 
@@ -1649,9 +1846,20 @@ hipError_t launch_foveated(const FovDesc& fd, int op, hipStream_t stream)
         if (!fd.f.tame) {
             if (push) FWRS_FOV_LAUNCH(kWild, true, kPush);
             else FWRS_FOV_LAUNCH(kWild, true, kFused);
+        } else if (fd.f.k == 1) {
+            if (push) FWRS_FOV_LAUNCH(1, true, kPush);
+            else FWRS_FOV_LAUNCH(1, true, kFused);
+        } else if (fd.f.k == 2) {
+            if (push) FWRS_FOV_LAUNCH(2, true, kPush);
+            else FWRS_FOV_LAUNCH(2, true, kFused);
         } else if (fd.f.k == 4) {
-            if (push) FWRS_FOV_LAUNCH(4, true, kPush);
-            else FWRS_FOV_LAUNCH(4, true, kFused);
+            if (store_streams(fd.f)) {
+                if (push) hipLaunchKernelGGL((foveated_kernel<4, true, kPush, 2>), grid, block, 0, stream, fd);
+                else hipLaunchKernelGGL((foveated_kernel<4, true, kFused, 2>), grid, block, 0, stream, fd);
+            } else {
+                if (push) hipLaunchKernelGGL((foveated_kernel<4, true, kPush, 0>), grid, block, 0, stream, fd);
+                else hipLaunchKernelGGL((foveated_kernel<4, true, kFused, 0>), grid, block, 0, stream, fd);
+            }
         } else {
             if (push) FWRS_FOV_LAUNCH(0, true, kPush);
             else FWRS_FOV_LAUNCH(0, true, kFused);
@@ -1682,21 +1890,10 @@ hipError_t launch_tick_args(const TickArgs& a, int kind, hipStream_t stream)
 {
     const uint32_t grid = a.head.total;
     if (grid == 0u) return hipSuccess;
-    if (kind == kTickGroups8)
-        hipLaunchKernelGGL(tick_args_kernel<kTickGroups8>, dim3(grid), dim3(kBlock), 0, stream, a);
-    else if (kind == kTickGroups)
-        hipLaunchKernelGGL(tick_args_kernel<kTickGroups>, dim3(grid), dim3(kBlock), 0, stream, a);
-    else
-        hipLaunchKernelGGL(tick_args_kernel<kTickAlone>, dim3(grid), dim3(kBlock), 0, stream, a);
+    hipLaunchKernelGGL(kTickArgsKernels[kind], dim3(grid), dim3(kBlock), 0, stream, a);
     return hipGetLastError();
 }
 
-void* tick_kernel_entry(int kind)
-{
-    if (kind == kTickGroups8) return reinterpret_cast<void*>(&tick_kernel<kTickGroups8>);
-    if (kind == kTickGroups) return reinterpret_cast<void*>(&tick_kernel<kTickGroups>);
-    return reinterpret_cast<void*>(&tick_kernel<kTickAlone>);
-}
-
+void* tick_kernel_entry(int kind) { return reinterpret_cast<void*>(kTickKernels[kind]); }
 
 }  // namespace fwrs
