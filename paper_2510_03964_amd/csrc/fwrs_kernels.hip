@@ -1195,167 +1195,184 @@ __global__ __launch_bounds__(64) void tick_fill_kernel(uint32_t* __restrict__ ta
 // frame's update as in the other kernels (Eq. 4, the bias, Alg. 2 per slot),
 // written densely to this frame's bank, and the resolve.  A gather from the
 // previous bank, so the banks alternate; every slot is rewritten.
+// Bound by its bytes (61 + 40k a pixel).  Sources, depth test and decisions run
+// with one lane per pixel, the records with one lane per slot, so gathers and the
+// dense stores are whole lines; those stores are non-temporal (nothing reads them
+// before the next frame).  Against one lane per pixel: 3840x2160 k = 4 370 -> 307 us
+// (322 with cached stores) = 6.0 TB/s, 1920x1080 k = 8 225 -> 139, Eq. 7 k = 4
+// 141 -> 101, 640x360 14.8 -> 11.0.
 // ---------------------------------------------------------------------------
 template <int SLOTS, bool PER_SLOT>
-__device__ __forceinline__ uint32_t pixel_reproject(const ReprojDesc& r, uint32_t x, uint32_t y)
+struct ReprojShare {                            // one wave's pixels
+    static constexpr int kBlocks = SLOTS > 0 ? (SLOTS + 3) / 4 : (kMaxK + 3) / 4;
+    uint4 pixel[64];                            // {p, source, inside | history kept << 1, replaced slots (shared w_sum)}
+    float4 colour[64];                          // the new colour, weight; then the resolve
+    uint32_t words[PER_SLOT ? 64 : 1][4 * kBlocks];    // Philox words, one per slot (per-slot modes)
+};
+
+template <int SLOTS, bool PER_SLOT>
+__device__ __forceinline__ void reproject_tile(const ReprojDesc& r, uint32_t item, uint32_t wave,
+                                               ReprojShare<SLOTS, PER_SLOT>& sh)
 {
     const FrameDesc& d = r.f;
-    const uint32_t p = y * d.width + x;
     constexpr bool kTame = SLOTS != kWild;
     constexpr int K = SLOTS > 0 ? SLOTS : 0;
-    const int kk = K ? K : (int)d.k;
-    constexpr int R = K ? K : 1;
+    constexpr uint32_t D = K == 4 ? 4u : K == 8 ? 2u : 1u;      // rounds loaded ahead
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t kk = K ? (uint32_t)K : d.k;
+    const uint32_t lg = group_log2<K>(kk), first = group_first<K>(kk);
+    const uint32_t j = lane & ((1u << lg) - 1u), per = 64u >> lg;
+    const bool slot = K || j < kk;
+    const bool aes = d.bias == kAes;
+    const float empty_slot = aes ? -INFINITY : 0.f;     // A-ES key / Eq. 7 sum of an empty slot
 
-    // 1. the motion-compensated source and the depth test
+    // 1. one lane per pixel: the motion-compensated source
+    uint32_t x, y;
+    const bool in = item_pixel_of(d, item, wave, lane, x, y);
+    if (!in) x = y = 0u;                                // lanes outside read pixel 0 and store nothing
+    const uint32_t p = y * d.width + x;
     const float2 mv = ld2<kNtColor>(r.motion + 2 * (size_t)p);
     const float dc = ld<kNtColor>(r.depth + p);
-    const float sx = ((float)x + 0.5f) - mv.x;
-    const float sy = ((float)y + 0.5f) - mv.y;
-    bool keep = false;
-    uint32_t q = 0u;
-    if (sx >= 0.0f && sx < (float)d.width && sy >= 0.0f && sy < (float)d.height) {
-        const uint32_t qx = (uint32_t)floorf(sx);
-        const uint32_t qy = (uint32_t)floorf(sy);
-        q = qy * d.width + qx;
-        const float dp = r.src_depth[q];
-        keep = fabsf(dc - dp) <= r.tol * dc;      // NaN (no previous frame) compares false
-    }
-
-    // 2. the history: the source reservoir, or the empty one
-    const float4* src = reinterpret_cast<const float4*>(r.src_rec) + (size_t)q * (size_t)kk;
-    const uint32_t* sidx = r.src_idx + (size_t)q * (size_t)kk;
-    float4 rv[R];
-    uint32_t iv[R];
-    float W[R];
-    const float4 empty = make_float4(0.f, 0.f, 0.f, 0.f);
-    const bool aes = d.bias == kAes;
-    const float empty_slot = aes ? -INFINITY : 0.f;      // A-ES key / Eq. 7 sum of an empty slot
-    // loads are unconditional (q = 0 is a valid pixel when the history is dropped) and the
-    // empty values are selected afterwards, so every load is a plain global load
-    if (K) {
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const float4 v = src[j];
-            const uint32_t i = sidx[j];
-            rv[j] = keep ? v : empty;
-            iv[j] = keep ? i : 0xFFFFFFFFu;
-            if (PER_SLOT) {
-                const float ws = r.src_wsum[(size_t)q * (size_t)kk + j];
-                W[j] = keep ? ws : empty_slot;
-            }
-        }
-    }
-    float W1 = 0.f;
-    uint32_t m = 0u;
-    {
-        const float ws = PER_SLOT ? 0.f : r.src_wsum[q];
-        const uint32_t mc = r.src_cnt[q];
-        W1 = keep ? ws : 0.f;
-        m = keep ? mc : 0u;
-    }
-
-    // 3. this frame's candidate
     const uint32_t lv = ld<kNtLevel>(d.level + p);
     const float* color = d.color + 3 * (size_t)p;
     const float c0 = ld<kNtColor>(color + 0);
     const float c1 = ld<kNtColor>(color + 1);
     const float c2 = ld<kNtColor>(color + 2);
+    const float sx = ((float)x + 0.5f) - mv.x;
+    const float sy = ((float)y + 0.5f) - mv.y;
+    const bool inside = sx >= 0.0f && sx < (float)d.width && sy >= 0.0f && sy < (float)d.height;
+    uint32_t q = 0u;                                    // a valid pixel where there is no source
+    if (inside) q = (uint32_t)floorf(sy) * d.width + (uint32_t)floorf(sx);
+    sh.pixel[lane] = make_uint4(p, q, 0u, 0u);
+    wave_lds_fence();
+
+    // the first rounds' source records, in flight over the pixels' arithmetic
+    // (unconditional; an empty history is selected afterwards)
+    float4 v[D];
+    uint32_t vi[D];
+    float vw[D];
+    auto load = [&](uint32_t b, float4& rec, uint32_t& idx, float& val) {
+        const size_t at = (size_t)sh.pixel[b + (lane >> lg)].y * kk + (slot ? j : 0u);
+        rec = ld4<0u>(reinterpret_cast<const float4*>(r.src_rec) + at);
+        idx = ld<0u>(r.src_idx + at);
+        val = PER_SLOT ? ld<kNtWsumLd>(r.src_wsum + at) : 0.f;
+    };
+#pragma unroll
+    for (uint32_t u = 0; u < D; ++u)
+        if (u * per < 64u) load(u * per, v[u], vi[u], vw[u]);
+
+    // the depth test, the frame's candidate and (shared w_sum) the decisions
+    const float dp = r.src_depth[q];
+    const float ws = PER_SLOT ? 0.f : r.src_wsum[q];
+    const uint32_t mc = r.src_cnt[q];
     const float dx = ((float)x + 0.5f) - d.gx;
     const float dy = ((float)y + 0.5f) - d.gy;
     const float w = weight_eq4<kTame>(d.c, dx * dx + dy * dy, lv);
-    const float4 fresh = make_float4(w, c0, c1, c2);
-    // Eq. 7: a slot whose sample has the new pixel's colour has |dL| = 0 exactly
-    // (same_colour); neither Lab is evaluated for it
-    const bool bounded = lab_bounded(c0, c1, c2);
-    uint32_t same = 0u;
-    if (K && PER_SLOT && !aes) {
-#pragma unroll
-        for (int j = 0; j < R; ++j)
-            if (bounded && same_colour(rv[j], c0, c1, c2)) same |= 1u << j;
-    }
-    float3 lab_new = make_float3(0.f, 0.f, 0.f);
-    if (PER_SLOT && !aes && (!K || same != (1u << R) - 1u)) lab_new = rgb_to_lab(c0, c1, c2);
-    const float W1b = PER_SLOT ? 0.f : bias_shared<kTame>(W1, w, d.bias, d.c.decay);
-    const float s = W1b + w;
-
-    // 4. Alg. 2 per slot, dense stores to this frame's bank, resolve sums
-    float4* rec = reinterpret_cast<float4*>(d.rec) + (size_t)p * (size_t)kk;
-    uint32_t* idx = d.idx + (size_t)p * (size_t)kk;
-    float S = 0.f, a0 = 0.f, a1 = 0.f, a2 = 0.f;
+    const bool keep = inside && fabsf(dc - dp) <= r.tol * dc;      // NaN (no previous frame) compares false
+    const uint32_t m = keep ? mc : 0u;
+    float s = 0.f;
     uint32_t tk = 0u;
-    uint4 words = make_uint4(0u, 0u, 0u, 0u);
+    if constexpr (PER_SLOT) {
+        for (uint32_t b = 0; 4u * b < kk; ++b) {
+            const uint4 t = philox4x32_10(p, d.t, b, d.seed, d.stream_id);
+            *reinterpret_cast<uint4*>(&sh.words[lane][4u * b]) = t;
+        }
+    } else {
+        const float W1b = bias_shared<kTame>(keep ? ws : 0.f, w, d.bias, d.c.decay);
+        s = W1b + w;
+        if constexpr (K > 0) tk = decide_words<K>(philox_words<K>(d, p), W1b, s);
+        else tk = decide_any<kTame>(d, p, W1b, s);
+    }
+    sh.pixel[lane] = make_uint4(p, q, (in ? 1u : 0u) | (keep ? 2u : 0u), tk);
+    sh.colour[lane] = make_float4(c0, c1, c2, w);
+    const uint32_t flushed = (uint32_t)__builtin_popcountll(__ballot(in && !keep));
+    wave_lds_fence();
+
+    // 2. one lane per slot: Alg. 2, dense stores to this frame's bank, resolve sums
+    uint32_t slots = 0u, changed = 0u;
+    for (uint32_t b0 = 0; b0 < 64u; b0 += D * per)
 #pragma unroll
-    for (int j = 0; j < kk; ++j) {
-        float4 v;
-        uint32_t vi;
-        float Wj = 0.f;
-        if (K) {
-            v = rv[K ? j : 0];
-            vi = iv[K ? j : 0];
-            if (PER_SLOT) Wj = W[K ? j : 0];
-        } else {
-            const float4 sv = src[j];
-            const uint32_t si = sidx[j];
-            v = keep ? sv : empty;
-            vi = keep ? si : 0xFFFFFFFFu;
-            if (PER_SLOT) {
-                const float ws = r.src_wsum[(size_t)q * (size_t)kk + j];
-                Wj = keep ? ws : empty_slot;
-            }
-        }
-        if ((j & 3) == 0) words = philox4x32_10(p, d.t, (uint32_t)(j >> 2), d.seed, d.stream_id);
-        const uint32_t word = (j & 3) == 0 ? words.x : (j & 3) == 1 ? words.y : (j & 3) == 2 ? words.z : words.w;
-        float W1j = W1b, sj = s;
+    for (uint32_t u = 0; u < D; ++u) {
+        const uint32_t b = b0 + u * per;
+        if (b >= 64u) break;
+        const uint32_t e = b + (lane >> lg);
+        const uint4 px = sh.pixel[e];
+        const float4 c = sh.colour[e];
+        const size_t at = (size_t)px.x * kk + (slot ? j : 0u);
+        const bool kept = (px.z & 2u) != 0u;
+        float4 t = kept ? v[u] : make_float4(0.f, 0.f, 0.f, 0.f);
+        uint32_t ti = kept ? vi[u] : 0xFFFFFFFFu;
+        const float Wj = kept ? vw[u] : empty_slot;
+        if (b + D * per < 64u) load(b + D * per, v[u], vi[u], vw[u]);
         bool take;
-        if (PER_SLOT && aes) {
-            const float kn = kTame ? div_rn(log2_unit(word), w) : log2_unit(word) / w;
-            take = kn > Wj;
-            st<kNtWsumSt>(d.wsum + (size_t)p * (size_t)kk + j, take ? kn : Wj);
+        float sj = 0.f;
+        if constexpr (!PER_SLOT) {
+            take = ((px.w >> j) & 1u) != 0u;
         } else {
-            if (PER_SLOT) {
-                const bool same_j = K ? ((same >> j) & 1u) != 0u : bounded && same_colour(v, c0, c1, c2);
+            const uint32_t word = sh.words[e][slot ? j : 0u];
+            if (aes) {
+                const float kn = kTame ? div_rn(log2_unit(word), c.w) : log2_unit(word) / c.w;
+                take = kn > Wj;
+                sj = take ? kn : Wj;
+            } else {
+                // Eq. 7: a sample with the new pixel's colour has |dL| = 0 exactly (same_colour)
                 float dl = 0.0f;
-                if (!same_j) dl = delta_l(v.y, v.z, v.w, lab_new);
-                W1j = bias_eq7<kTame>(Wj, w, dl);
-                sj = W1j + w;
-                st<kNtWsumSt>(d.wsum + (size_t)p * (size_t)kk + j, sj);
+                if (!(lab_bounded(c.x, c.y, c.z) && same_colour(t, c.x, c.y, c.z)))
+                    dl = delta_l(t.y, t.z, t.w, rgb_to_lab(c.x, c.y, c.z));
+                const float W1j = bias_eq7<kTame>(Wj, c.w, dl);
+                sj = W1j + c.w;
+                take = takes<kTame>(word, sj, W1j);
             }
-            take = takes<kTame>(word, sj, W1j);
         }
+        const bool own = slot && (px.z & 1u) != 0u;
+        take = take && own;
         if (take) {
-            tk |= 1u << j;
-            v = fresh;
-            vi = d.t;
+            t = make_float4(c.w, c.x, c.y, c.z);
+            ti = d.t;
         }
-        st4<kNtRecSt>(rec + j, v);
-        st<kNtIdxSt>(idx + j, vi);
-        S = S + v.x;
-        a0 = a0 + v.x * v.y;
-        a1 = a1 + v.x * v.z;
-        a2 = a2 + v.x * v.w;
+        const uint64_t took = __ballot(take);
+        slots += (uint32_t)__builtin_popcountll(took);
+        const bool any = ((took >> (lane & ~((1u << lg) - 1u))) & ((1ull << (1u << lg)) - 1ull)) != 0u;
+        changed += (uint32_t)__builtin_popcountll(__ballot(any && j == 0u));
+        if (d.out) {                                    // uniform
+            const float rs = resolve_scale<kTame>(group_sum<K>(t.x, kk));
+            const float q0 = group_sum<K>(t.x * t.y, kk) * rs;
+            const float q1 = group_sum<K>(t.x * t.z, kk) * rs;
+            const float q2 = group_sum<K>(t.x * t.w, kk) * rs;
+            if (j == first) sh.colour[e] = make_float4(q0, q1, q2, 0.f);
+        }
+        if (own) {
+            st4<kNtOut>(reinterpret_cast<float4*>(d.rec) + at, t);
+            st<kNtOut>(d.idx + at, ti);
+            if (PER_SLOT) st<kNtWsumSt>(d.wsum + at, sj);
+        }
     }
-    if (!PER_SLOT) st<kNtWsumSt>(d.wsum + p, s);
-    st<kNtWsumSt>(r.cnt + p, m + 1u);
-    st<kNtWsumSt>(r.depth_out + p, dc);
-    if (d.out) {
-        const float rs = resolve_scale<kTame>(S);
-        float* o = d.out + 3 * (size_t)p;
-        st<kNtOut>(o + 0, a0 * rs);
-        st<kNtOut>(o + 1, a1 * rs);
-        st<kNtOut>(o + 2, a2 * rs);
+    wave_lds_fence();
+
+    // 3. one lane per pixel
+    if (in) {
+        if (!PER_SLOT) st<kNtWsumSt>(d.wsum + p, s);
+        st<kNtWsumSt>(r.cnt + p, m + 1u);
+        st<kNtWsumSt>(r.depth_out + p, dc);
+        if (d.out) {
+            const float4 o4 = sh.colour[lane];
+            float* o = d.out + 3 * (size_t)p;
+            st<kNtOut>(o + 0, o4.x);
+            st<kNtOut>(o + 1, o4.y);
+            st<kNtOut>(o + 2, o4.z);
+        }
     }
-    return __popc(tk) + (tk ? 0x10000u : 0u) + (keep ? 0u : 0x1000000u);
+    if (d.stats && (changed || flushed)) add_counts(d.stats, slots, changed, flushed);
 }
 
 template <int K, bool PER_SLOT>
-__global__ __launch_bounds__(kBlock) void reproject_kernel(ReprojDesc r)
+__global__ __launch_bounds__(kBlock, 6) void reproject_kernel(ReprojDesc r)
 {
-    const FrameDesc& d = r.f;
+    __shared__ ReprojShare<K, PER_SLOT> share[kBlock / 64];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // forward order every frame: this dense pass (221 B per pixel) gains nothing
     // from the Infinity Cache and streams slightly slower backwards
-    uint32_t x, y, n = 0u;
-    if (item_pixel(d, blockIdx.x, x, y)) n = pixel_reproject<K, PER_SLOT>(r, x, y);
-    if (d.stats) add_stats(d.stats, n);
+    reproject_tile<K, PER_SLOT>(r, blockIdx.x, wave, share[wave]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1757,6 +1774,14 @@ hipError_t launch_reproject(const ReprojDesc& r, hipStream_t stream)
         case kWild:
             if (eq7) hipLaunchKernelGGL((reproject_kernel<kWild, true>), grid, block, 0, stream, r);
             else hipLaunchKernelGGL((reproject_kernel<kWild, false>), grid, block, 0, stream, r);
+            break;
+        case 1:
+            if (eq7) hipLaunchKernelGGL((reproject_kernel<1, true>), grid, block, 0, stream, r);
+            else hipLaunchKernelGGL((reproject_kernel<1, false>), grid, block, 0, stream, r);
+            break;
+        case 2:
+            if (eq7) hipLaunchKernelGGL((reproject_kernel<2, true>), grid, block, 0, stream, r);
+            else hipLaunchKernelGGL((reproject_kernel<2, false>), grid, block, 0, stream, r);
             break;
         case 4:
             if (eq7) hipLaunchKernelGGL((reproject_kernel<4, true>), grid, block, 0, stream, r);
