@@ -115,17 +115,22 @@ bool tile_ok(int tx, int ty)
     return lx + ly >= 6 && lx + ly <= 8;
 }
 
+// Makes `dev` the current device for a scope; a caller already on it pays for one
+// query.
 struct DeviceGuard {
     int prev = -1;
     bool ok = true;
+    bool changed = false;
     explicit DeviceGuard(int dev)
     {
         if (hipGetDevice(&prev) != hipSuccess) { ok = false; return; }
-        if (prev != dev && hipSetDevice(dev) != hipSuccess) ok = false;
+        if (prev == dev) return;
+        ok = hipSetDevice(dev) == hipSuccess;
+        changed = ok;
     }
     ~DeviceGuard()
     {
-        if (ok && prev >= 0) (void)hipSetDevice(prev);
+        if (changed) (void)hipSetDevice(prev);
     }
 };
 

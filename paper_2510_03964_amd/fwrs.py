@@ -207,7 +207,7 @@ def _stream_handle(stream) -> int | None:
 
 
 def _ptr(t) -> int:
-    return int(t.data_ptr())
+    return t.data_ptr()
 
 
 def _f32(t) -> bool:
@@ -240,6 +240,11 @@ class Reservoir:
     def __init__(self, width: int, height: int, k: int, params: Params | None = None, stream=None, arena=None):
         self._L = load()
         self.width, self.height, self.k = int(width), int(height), int(k)
+        import torch                       # the checks of every frame compare its dtype objects
+
+        self._float32, self._uint8 = torch.float32, torch.uint8
+        self._shape2 = (self.height, self.width)
+        self._shape3 = (self.height, self.width, 3)
         self.params = params if params is not None else default_params(width)
         self._arena = arena
         h = C.c_void_p()
@@ -286,15 +291,15 @@ class Reservoir:
 
     def _check_frame(self, color, level) -> None:
         H, W = self.height, self.width
-        if tuple(color.shape) != (H, W, 3) or not _f32(color) or not color.is_contiguous():
+        if color.shape != self._shape3 or color.dtype is not self._float32 or not color.is_contiguous():
             raise ValueError(f"color must be contiguous float32 [{H}, {W}, 3]")
-        if tuple(level.shape) != (H, W) or not _u8(level) or not level.is_contiguous():
+        if level.shape != self._shape2 or level.dtype is not self._uint8 or not level.is_contiguous():
             raise ValueError(f"level must be contiguous uint8 [{H}, {W}]")
         if not (color.is_cuda and level.is_cuda):
             raise ValueError("color and level must be device tensors")
 
     def _check_out(self, out) -> None:
-        if tuple(out.shape) != (self.height, self.width, 3) or not _f32(out) or not out.is_contiguous():
+        if out.shape != self._shape3 or out.dtype is not self._float32 or not out.is_contiguous():
             raise ValueError("out must be contiguous float32 [H, W, 3]")
         if not out.is_cuda:
             raise ValueError("out must be a device tensor")
