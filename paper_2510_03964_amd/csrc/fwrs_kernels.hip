@@ -1037,7 +1037,7 @@ __global__ __launch_bounds__(kBlock, T ? kFrameWaves : 1) void frame_kernel(Fram
 // a lone frame runs the single-frame per-pixel code for the frame's slot count
 // and op (kFused, kCached or kFill); an item of a group runs pixel_group (op
 // kGroup), or else (run-time slot counts, per-slot modes) each of the group's
-// frames in turn through the store, every pixel in the same thread, so each
+// frames in turn through the store, every pixel in the same wave, so each
 // frame reads what the one before wrote.
 // ---------------------------------------------------------------------------
 // A wave's LDS in the batched kernel: a list (stream_tiles), in ticks with
@@ -1116,6 +1116,13 @@ __device__ __forceinline__ void tick_group_item(const FrameDesc& d, const FrameD
     }
     for (uint32_t f = 0; f < d.nf; ++f) {
         const FrameDesc& df = f == 0u ? d : later[f - 1u];
+        // a pixel's record may pass from one lane to another between frames: the
+        // stores of the frame before are done before this one loads
+        if (f) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        }
         tick_item<PS>(df, local, wave, sh);
     }
 }
@@ -1494,15 +1501,15 @@ __global__ __launch_bounds__(kBlock) void mip_kernel(MipArgs a)
 // distances to the gaze, widened by 2^-10 relative so that rounding can only make
 // it need more.
 //
-// Bound by LDS reads (13 of 4 bytes per float and row at radius 6), next by the
-// vector ALU (a fused multiply-add would round differently).  One thread per pixel
-// column with a window of row sums took 276 instructions per pixel and walked row,
-// and its few waves left the chip idle below 4K.  The generator call at 2560x1440
-// went from 68 to 51 us (these levels 53 to 36), at 1920x1080 from 42 to 33, at
-// 256x256 from 20 to 9.5, at 3840x2160 from 121 to 104.  Four neighbouring floats
-// per lane read 2.6 times less LDS but leave 1.3 waves per SIMD at 2560x1440 (52 us;
-// 99 at 3840x2160); two floats: 57 and 117; the two levels in blocks of their own:
-// 51 and 108.
+// Bound by the vector ALU (a fused multiply-add would round differently), at
+// about 60% of its issue rate: 84 registers leave 5 waves per SIMD, and 6 spill (51
+// -> 61 us).  One thread per pixel column with a window of row sums took 276
+// instructions per pixel and walked row, and its few waves left the chip idle
+// below 4K.  The generator call at 2560x1440 went from 68 to 51 us (these levels 53
+// to 36), at 1920x1080 from 42 to 33, at 256x256 from 20 to 9.5, at 3840x2160 from
+// 121 to 104.  Four neighbouring floats per lane read 2.6 times less LDS but leave
+// 1.3 waves per SIMD at 2560x1440 (52 us; 99 at 3840x2160); two floats: 57 and 117;
+// the two levels in blocks of their own: 51 and 108; two rows a batch: 50 and 107.
 struct GaussArgs {
     const float* src;
     float* dst;
