@@ -345,12 +345,10 @@ __device__ __forceinline__ void pixel_group(const FrameDesc& d0, const FrameDesc
 }
 
 // ---------------------------------------------------------------------------
-// One work item (256 pixels).  The wave index is made explicit as a uniform
-// value so the tile arithmetic runs on the scalar unit.
-// ---------------------------------------------------------------------------
-// Pixel of this thread in work item `item`; false outside the image (or past
-// the frame's last item).  The wave index is made explicit as a uniform value
+// Pixel of a lane of wave `wave` in work item `item` (256 pixels); false outside
+// the image (or past the frame's last item).  The wave index is a uniform value,
 // so the tile arithmetic runs on the scalar unit.
+// ---------------------------------------------------------------------------
 __device__ __forceinline__ bool item_pixel_of(const FrameDesc& d, uint32_t item, uint32_t wave, uint32_t lane,
                                               uint32_t& x, uint32_t& y)
 {
@@ -364,12 +362,6 @@ __device__ __forceinline__ bool item_pixel_of(const FrameDesc& d, uint32_t item,
     x = (tx << d.tile_x_log2) + (local & ((1u << d.tile_x_log2) - 1u));
     y = (ty << d.tile_y_log2) + (local >> d.tile_x_log2);
     return item < d.items && y < d.height && x < d.width;
-}
-
-__device__ __forceinline__ bool item_pixel(const FrameDesc& d, uint32_t item, uint32_t& x, uint32_t& y)
-{
-    const uint32_t tid = threadIdx.x;
-    return item_pixel_of(d, item, __builtin_amdgcn_readfirstlane(tid >> 6), tid & 63u, x, y);
 }
 
 // Sum of v over the wave, in every lane: five row-wise steps by data-parallel
@@ -1191,9 +1183,6 @@ __global__ __launch_bounds__(64) void tick_fill_kernel(uint32_t* __restrict__ ta
     if (f.write_head && threadIdx.x < 4u) st<0u>(table + threadIdx.x, reinterpret_cast<const uint32_t*>(&f.head)[threadIdx.x]);
 }
 
-// ---------------------------------------------------------------------------
-// Store initialisation: the empty reservoir.
-// ---------------------------------------------------------------------------
 // ---------------------------------------------------------------------------
 // Reprojected frame (Sec. 4.3).  Pixel p continues the reservoir of the pixel
 // containing its centre moved back by its motion vector, if that point is in
