@@ -747,7 +747,7 @@ int check_tick(const fwrs_frame* frames, int n, int max_frames, int device)
 }
 
 // Scratch of the tick layout for up to m entries: kTickWorkInts * m ints.
-constexpr size_t kTickWorkInts = 7;
+constexpr size_t kTickWorkInts = 6;
 struct TickWork {
     int* group;     // [entry] its context's group
     int* count;     // [group] entries
@@ -755,13 +755,11 @@ struct TickWork {
     int* slot;      // [group] the leader's table index
     int* base;      // [group] table index of the group's second frame
     int* plane;     // [group] before the entry being laid out: 1 the resolve plane is whole, 2 the context is tame
-    int* tame;      // [group] its context is tame after all its entries
     TickWork(int* w, size_t m)
-        : group(w), count(w + m), pos(w + 2 * m), slot(w + 3 * m), base(w + 4 * m), plane(w + 5 * m),
-          tame(w + 6 * m) {}
+        : group(w), count(w + m), pos(w + 2 * m), slot(w + 3 * m), base(w + 4 * m), plane(w + 5 * m) {}
 };
 
-// Whether pixel_group runs x's groups of tame frames: compile-time slot counts and one w_sum per pixel.
+// Whether pixel_group runs x's groups: compile-time slot counts and one w_sum per pixel.
 bool group_kernel(const fwrs_ctx* x)
 {
     return (x->k == 1 || x->k == 2 || x->k == 4 || x->k == 8) && !fwrs::per_slot_mode(x->prm.bias_mode);
@@ -792,10 +790,8 @@ int layout_tick(const fwrs_frame* frames, int n, bool reverse, TileFn tile, Tick
             w.count[groups] = 0;
             w.pos[groups] = 0;
             w.plane[groups] = (x->res_valid ? 1 : 0) | (x->tame ? 2 : 0);
-            w.tame[groups] = x->tame ? 1 : 0;
             ++groups;
         }
-        w.tame[x->tick_group] = tame_at(x, w.tame[x->tick_group] != 0, frames[i].gaze_x, frames[i].gaze_y) ? 1 : 0;
         w.group[i] = x->tick_group;
         w.count[x->tick_group] += 1;
         if ((uint64_t)x->t + (uint64_t)w.count[x->tick_group] > 0xFFFFFFFFull) return FWRS_E_STATE;
@@ -820,7 +816,7 @@ int layout_tick(const fwrs_frame* frames, int n, bool reverse, TileFn tile, Tick
         d.t = x->t + (uint32_t)at;
         const bool plane = (w.plane[g] & 1) != 0;
         const bool tame = tame_at(x, (w.plane[g] & 2) != 0, f.gaze_x, f.gaze_y);
-        const int op = nf > 1 && w.tame[g] != 0 && group_kernel(x) ? fwrs::kOpGroup : fused_op_at(x, d.t, plane);
+        const int op = nf > 1 && group_kernel(x) ? fwrs::kOpGroup : fused_op_at(x, d.t, plane);
         w.plane[g] = (plane_after(x, op) ? 1 : 0) | (tame ? 2 : 0);
         d.tame = tame ? 1u : 0u;
         if (nf > 1 && groups_kind != fwrs::kTickGroups8)

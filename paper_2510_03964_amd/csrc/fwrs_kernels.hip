@@ -143,13 +143,13 @@ __device__ __forceinline__ Words<K> philox_words(const FrameDesc& d, uint32_t p)
     return out;
 }
 
-template <int K>
+template <int K, bool TAME>
 __device__ __forceinline__ uint32_t decide_words(const Words<K>& words, float W1b, float s)
 {
     uint32_t mask = 0u;
 #pragma unroll
     for (int j = 0; j < K; ++j)
-        if (takes<true>(words.w[j], s, W1b)) mask |= 1u << j;
+        if (takes<TAME>(words.w[j], s, W1b)) mask |= 1u << j;
     return mask;
 }
 
@@ -171,24 +171,72 @@ __device__ __forceinline__ uint32_t decide_any(const FrameDesc& d, uint32_t p, f
     return mask;
 }
 
-// Slot-count argument of the per-pixel code: a count the code is compiled for
-// (its record in registers), 0 for any count (streamed slot by slot), or kWild:
-// any count with the general division, root and variate test, for the frames of
-// a context that is not tame (frame_tame).
-constexpr int kWild = -1;
+// The Eq. 4 weight in two parts, as weight_outside and select_eq4.
+//
+// The frames of a context that is not tame (frame_tame) take the general
+// division, root and variate test in the same kernels, behind branches on a
+// uniform value, so they run at the compiled slot counts like any other frame.
+// The branches stand where no load is waited for: one around the arithmetic
+// before the level is needed, one after w_sum is there.
+__device__ __forceinline__ float weight_part(const FrameDesc& d, uint32_t x, uint32_t y, float& e)
+{
+    const float dx = ((float)x + 0.5f) - d.gx;
+    const float dy = ((float)y + 0.5f) - d.gy;
+    if (d.tame) return weight_outside<true>(d.c, dx * dx + dy * dy, e);
+    return weight_outside<false>(d.c, dx * dx + dy * dy, e);
+}
 
-// The resolve of a record held in registers: sum_j w_j col_j / sum_j w_j, the
-// sums taken in slot order; 0 for a record with no weight (only the empty
-// reservoir: every kept weight is > 0).
+__device__ __forceinline__ float frame_weight(const FrameDesc& d, uint32_t x, uint32_t y, uint32_t lv)
+{
+    float e;
+    const float o = weight_part(d, x, y, e);
+    return select_eq4(d.c, o, e, lv);
+}
+
+// The bias of the sum W for a candidate of weight w, the sum s after the frame and
+// the slots that take the candidate.
+template <int K, bool TAME>
+__device__ __forceinline__ uint32_t decide_as(const FrameDesc& d, uint32_t p, const Words<K ? K : 1>& words, float W,
+                                              float w, float& s)
+{
+    const float W1b = bias_shared<TAME>(W, w, d.bias, d.c.decay);
+    s = W1b + w;
+    if constexpr (K > 0) return decide_words<K, TAME>(words, W1b, s);
+    else return decide_any<TAME>(d, p, W1b, s);
+}
+
+// A pixel's decision: from its sum W before the frame to the weight w, the sum s
+// after it and the slots that take the candidate.
+template <int K>
+__device__ __forceinline__ uint32_t decide(const FrameDesc& d, uint32_t x, uint32_t y, uint32_t p, uint32_t lv,
+                                           float W, float& w, float& s)
+{
+    Words<K ? K : 1> words;
+    if constexpr (K > 0) words = philox_words<K>(d, p);
+    w = frame_weight(d, x, y, lv);
+    if (d.tame) return decide_as<K, true>(d, p, words, W, w, s);
+    return decide_as<K, false>(d, p, words, W, w, s);
+}
+
+// 1 / S for the resolve sum_j w_j col_j / sum_j w_j, the sums taken in slot
+// order; 0 for a record with no weight (only the empty reservoir: every kept
+// weight is > 0).
 template <bool TAME>
-__device__ __forceinline__ float resolve_scale(float S)
+__device__ __forceinline__ float resolve_scale_as(float S)
 {
     const float rs = TAME ? rcp_rn(S) : 1.0f / S;
     return S > 0.0f ? rs : 0.0f;
 }
 
+__device__ __forceinline__ float resolve_scale(const FrameDesc& d, float S)
+{
+    if (d.tame) return resolve_scale_as<true>(S);
+    return resolve_scale_as<false>(S);
+}
+
+// The resolve of a record held in registers.
 template <int R>
-__device__ __forceinline__ void resolve_slots(const float4 (&r)[R], float& q0, float& q1, float& q2)
+__device__ __forceinline__ void resolve_slots(const FrameDesc& d, const float4 (&r)[R], float& q0, float& q1, float& q2)
 {
     float S = 0.f, a0 = 0.f, a1 = 0.f, a2 = 0.f;
 #pragma unroll
@@ -198,7 +246,7 @@ __device__ __forceinline__ void resolve_slots(const float4 (&r)[R], float& q0, f
         a1 = a1 + r[j].x * r[j].z;
         a2 = a2 + r[j].x * r[j].w;
     }
-    const float rs = resolve_scale<true>(S);
+    const float rs = resolve_scale(d, S);
     q0 = a0 * rs;
     q1 = a1 * rs;
     q2 = a2 * rs;
@@ -249,7 +297,7 @@ struct GroupPixel {
                     tj[j] = d.t;
                 }
             dirty |= tk;
-            resolve_slots<K>(r, q0, q1, q2);
+            resolve_slots<K>(d, r, q0, q1, q2);
             slots += (uint32_t)__popc(tk);
             changed += 1u;
         }
@@ -290,7 +338,7 @@ __device__ __forceinline__ void pixel_group(const FrameDesc& d0, const FrameDesc
     } else if (!empty) {
 #pragma unroll
         for (int j = 0; j < K; ++j) g.r[j] = ld4<kNtRecLd>(rec + j);
-        resolve_slots<K>(g.r, g.q0, g.q1, g.q2);
+        resolve_slots<K>(d0, g.r, g.q0, g.q1, g.q2);
     }
 
     // the decided frame still to apply
@@ -301,14 +349,8 @@ __device__ __forceinline__ void pixel_group(const FrameDesc& d0, const FrameDesc
         uint32_t lv_next = 0u;
         if (f + 1u < nf) lv_next = ld<kNtLevel>(later[f].level + p);
         // the decision: Eq. 4 weight, bias, Alg. 2 per slot
-        const float dx = ((float)x + 0.5f) - d.gx;
-        const float dy = ((float)y + 0.5f) - d.gy;
-        float e = 0.f;
-        const float outside = weight_outside<true>(d.c, dx * dx + dy * dy, e);
-        const float w = select_eq4(d.c, outside, e, lv);
-        const float W1b = bias_shared<true>(W1, w, d.bias, d.c.decay);
-        const float s = W1b + w;
-        const uint32_t tk = decide_words<K>(philox_words<K>(d, p), W1b, s);
+        float w, s;
+        const uint32_t tk = decide<K>(d, x, y, p, lv, W1, w, s);
         W1 = s;
         // its colour, and at the pixel's first replacement the slots it keeps
         const float* cp = d.color + (tk ? 3 * (size_t)p : 0);
@@ -474,7 +516,8 @@ __device__ __forceinline__ uint32_t group_first(uint32_t kk)
 }
 
 // 0 + v_0 + v_1 + ... + v_(kk-1) over a group of lanes, added in lane order (K: as
-// kk where known, else 0).  Valid in the quad of group_first.
+// kk where known, else 0).  Lanes past the slots hold +0, which leaves a sum that
+// started at +0 as it is.  Valid in the quad of group_first.
 template <int K>
 __device__ __forceinline__ float group_sum(float v, uint32_t kk)
 {
@@ -493,9 +536,9 @@ __device__ __forceinline__ float group_sum(float v, uint32_t kk)
             // the sum so far, from the quad below (row_shr:4)
             if (j) s = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, s), 0x114, 0xF, 0xF, true));
             s = s + v0;
-            if (K || j + 1u < kk) s = s + v1;
-            if (K || j + 2u < kk) s = s + v2;
-            if (K || j + 3u < kk) s = s + v3;
+            s = s + v1;
+            s = s + v2;
+            s = s + v3;
         }
     }
     return s;
@@ -511,11 +554,9 @@ __device__ __forceinline__ float group_sum(float v, uint32_t kk)
 // plane; kIncremental writes the output here.  Returns the lane's replaced slots.
 // (Loading 2, 4 or 8 rounds ahead of the first: within 1% at 2, slower beyond,
 // for the registers.)
-template <int SLOTS, int OP, bool FOV>
+template <int K, int OP, bool FOV, bool TAME>
 __device__ __forceinline__ uint32_t listed_pixels(const FrameDesc& d, const FovSrc* fs, uint4* list, uint32_t n)
 {
-    constexpr bool kTame = SLOTS != kWild;
-    constexpr int K = SLOTS > 0 ? SLOTS : 0;
     constexpr bool kResolves = OP != kPush, kUpdates = OP != kResolve;
     constexpr bool kWhole = OP == kFused || OP == kFill;
     const uint32_t lane = threadIdx.x & 63u;
@@ -533,6 +574,7 @@ __device__ __forceinline__ uint32_t listed_pixels(const FrameDesc& d, const FovS
         const size_t s = (size_t)p * kk + (slot ? j : 0u);
         float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
         if (kResolves && !empty) r = ld4<kNtRecLd>(reinterpret_cast<const float4*>(d.rec) + s);
+        if (!slot) r = make_float4(0.f, 0.f, 0.f, 0.f);
         bool take = false;
         if constexpr (kUpdates) {
             float c0, c1, c2;
@@ -562,7 +604,7 @@ __device__ __forceinline__ uint32_t listed_pixels(const FrameDesc& d, const FovS
         }
         float q0 = 0.f, q1 = 0.f, q2 = 0.f;
         if constexpr (kResolves) {
-            const float rs = resolve_scale<kTame>(group_sum<K>(r.x, kk));
+            const float rs = resolve_scale_as<TAME>(group_sum<K>(r.x, kk));
             q0 = group_sum<K>(r.x * r.y, kk) * rs;
             q1 = group_sum<K>(r.x * r.z, kk) * rs;
             q2 = group_sum<K>(r.x * r.w, kk) * rs;
@@ -597,12 +639,10 @@ __device__ __forceinline__ uint32_t listed_pixels(const FrameDesc& d, const FovS
 
 // The wave's 64 T pixels of work items item0 .. item0 + T - 1; list has room for
 // 64 T entries.  Returns the wave's (uniform) replaced slots + 2^16 x changed pixels.
-template <int SLOTS, int OP, int T, bool FOV = false>
+template <int K, int OP, int T, bool FOV = false>
 __device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t item0, uint32_t wave, uint4* list,
                                                  const FovSrc* fs = nullptr)
 {
-    constexpr bool kTame = SLOTS != kWild;
-    constexpr int K = SLOTS > 0 ? SLOTS : 0;
     constexpr bool kUpdates = OP != kResolve;
     constexpr bool kAll = OP == kFused || OP == kFill || OP == kResolve;    // every pixel is listed
     constexpr bool kRow = OP == kCached || kAll;                            // the output leaves by rows
@@ -634,13 +674,8 @@ __device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t it
         uint32_t tk = 0u;
         float w = 0.f;
         if constexpr (kUpdates) {
-            const float dx = ((float)x[t] + 0.5f) - d.gx;
-            const float dy = ((float)y[t] + 0.5f) - d.gy;
-            w = weight_eq4<kTame>(d.c, dx * dx + dy * dy, lv[t]);
-            const float W1b = bias_shared<kTame>(W[t], w, d.bias, d.c.decay);
-            const float s = W1b + w;
-            if constexpr (K > 0) tk = decide_words<K>(philox_words<K>(d, p[t]), W1b, s);
-            else tk = decide_any<kTame>(d, p[t], W1b, s);
+            float s;
+            tk = decide<K>(d, x[t], y[t], p[t], lv[t], W[t], w, s);
             if (!in[t]) tk = 0u;
             W[t] = s;
         }
@@ -655,7 +690,10 @@ __device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t it
     }
     wave_lds_fence();
     uint32_t slots = 0u;
-    if (n) slots = listed_pixels<SLOTS, OP, FOV>(d, fs, list, n);
+    if (n) {
+        if (OP == kPush || d.tame) slots = listed_pixels<K, OP, FOV, true>(d, fs, list, n);
+        else slots = listed_pixels<K, OP, FOV, false>(d, fs, list, n);
+    }
     if (changed) slots = wave_sum(slots);
     wave_lds_fence();
 #pragma unroll
@@ -682,6 +720,29 @@ __device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t it
         }
     }
     return slots + (changed << 16);
+}
+
+// The A-ES key log2(u) / w of a candidate.
+__device__ __forceinline__ float aes_key(const FrameDesc& d, uint32_t word, float w)
+{
+    const float l = log2_unit(word);
+    if (d.tame) return div_rn(l, w);
+    return l / w;
+}
+
+// Eq. 7 and the slot's Alg. 2 decision: s is the slot's sum after the frame.
+template <bool TAME>
+__device__ __forceinline__ bool decide_eq7_as(uint32_t word, float W, float w, float dl, float& s)
+{
+    const float W1b = bias_eq7<TAME>(W, w, dl);
+    s = W1b + w;
+    return takes<TAME>(word, s, W1b);
+}
+
+__device__ __forceinline__ bool decide_eq7(const FrameDesc& d, uint32_t word, float W, float w, float dl, float& s)
+{
+    if (d.tame) return decide_eq7_as<true>(word, W, w, dl, s);
+    return decide_eq7_as<false>(word, W, w, dl, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -718,21 +779,19 @@ __device__ __forceinline__ float4 ld4_streamed(const float4* p)
     return make_float4(v.x, v.y, v.z, v.w);
 }
 
-template <int SLOTS>
+template <int K>
 struct PerSlotShare {                           // one wave's pixels
-    static constexpr int kBlocks = SLOTS > 0 ? (SLOTS + 3) / 4 : (kMaxK + 3) / 4;
+    static constexpr int kBlocks = K ? (K + 3) / 4 : (kMaxK + 3) / 4;
     uint2 pixel[64];                            // {p, inside}
     float4 colour[64];                          // the new colour, weight; then the resolve, changed
     uint32_t words[64][4 * kBlocks];            // Philox words, one per slot
 };
 
-template <int SLOTS, int OP, bool FOV = false, bool STREAMED = false>
+template <int K, int OP, bool FOV = false, bool STREAMED = false>
 __device__ __forceinline__ uint32_t per_slot_tile(const FrameDesc& d, uint32_t item, uint32_t wave,
-                                                  PerSlotShare<SLOTS>& sh, const FovSrc* fs = nullptr)
+                                                  PerSlotShare<K>& sh, const FovSrc* fs = nullptr)
 {
     static_assert(OP == kPush || OP == kFused || OP == kIncremental, "the resolve-only pass is the same under every mode");
-    constexpr bool kTame = SLOTS != kWild;
-    constexpr int K = SLOTS > 0 ? SLOTS : 0;
     constexpr bool kResolves = OP != kPush;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t kk = K ? (uint32_t)K : d.k;
@@ -784,11 +843,7 @@ __device__ __forceinline__ uint32_t per_slot_tile(const FrameDesc& d, uint32_t i
         const uint4 r = philox4x32_10(p, d.t, b, d.seed, d.stream_id);
         *reinterpret_cast<uint4*>(&sh.words[lane][4u * b]) = r;
     }
-    {
-        const float dx = ((float)x + 0.5f) - d.gx;
-        const float dy = ((float)y + 0.5f) - d.gy;
-        sh.colour[lane] = make_float4(c0, c1, c2, weight_eq4<kTame>(d.c, dx * dx + dy * dy, lv));
-    }
+    sh.colour[lane] = make_float4(c0, c1, c2, frame_weight(d, x, y, lv));
     wave_lds_fence();
 
     // 2. one lane per slot
@@ -811,7 +866,7 @@ __device__ __forceinline__ uint32_t per_slot_tile(const FrameDesc& d, uint32_t i
         float s;
         if (aes) {
             // A-ES: the larger key log2(u) / w wins; the slot keeps its sample's key
-            const float kn = kTame ? div_rn(log2_unit(word), w) : log2_unit(word) / w;
+            const float kn = aes_key(d, word, w);
             take = kn > Wj;
             s = take ? kn : Wj;
         } else {
@@ -821,20 +876,19 @@ __device__ __forceinline__ uint32_t per_slot_tile(const FrameDesc& d, uint32_t i
             float dl = 0.0f;
             if (!(lab_bounded(c.x, c.y, c.z) && same_colour(r, c.x, c.y, c.z)))
                 dl = delta_l(r.y, r.z, r.w, rgb_to_lab(c.x, c.y, c.z));
-            const float W1b = bias_eq7<kTame>(Wj, w, dl);
-            s = W1b + w;
-            take = takes<kTame>(word, s, W1b);
+            take = decide_eq7(d, word, Wj, w, dl, s);
         }
         const bool own = slot && now.y != 0u;
         take = take && own;
         if (take) r = make_float4(w, c.x, c.y, c.z);
+        if (!slot) r = make_float4(0.f, 0.f, 0.f, 0.f);
         const uint64_t took = __ballot(take);
         slots += (uint32_t)__builtin_popcountll(took);
         const bool any = ((took >> (lane & ~((1u << lg) - 1u))) & ((1ull << (1u << lg)) - 1ull)) != 0u;
         changed += (uint32_t)__builtin_popcountll(__ballot(any && j == 0u));
         float q0 = 0.f, q1 = 0.f, q2 = 0.f;
         if constexpr (kResolves) {
-            const float rs = resolve_scale<kTame>(group_sum<K>(r.x, kk));
+            const float rs = resolve_scale(d, group_sum<K>(r.x, kk));
             q0 = group_sum<K>(r.x * r.y, kk) * rs;
             q1 = group_sum<K>(r.x * r.z, kk) * rs;
             q2 = group_sum<K>(r.x * r.w, kk) * rs;
@@ -904,9 +958,7 @@ __device__ __forceinline__ uint32_t pixel_per_slot(const FrameDesc& d, uint32_t 
         c1 = ld<kNtColor>(color + 1);
         c2 = ld<kNtColor>(color + 2);
     }
-    const float dx = ((float)x + 0.5f) - d.gx;
-    const float dy = ((float)y + 0.5f) - d.gy;
-    const float w = weight_eq4<true>(d.c, dx * dx + dy * dy, lv);
+    const float w = frame_weight(d, x, y, lv);
     const bool aes = d.bias == kAes;
     // Eq. 7: a slot whose sample has the new pixel's colour has |dL| = 0 exactly
     // (same_colour), so its Lab and CIE94 are not evaluated, nor the new
@@ -935,16 +987,14 @@ __device__ __forceinline__ uint32_t pixel_per_slot(const FrameDesc& d, uint32_t 
         float s;
         if (aes) {
             // A-ES: the larger key log2(u) / w wins; the slot keeps its sample's key
-            const float kn = div_rn(log2_unit(word), w);
+            const float kn = aes_key(d, word, w);
             take = kn > W1;
             s = take ? kn : W1;
         } else {
             // Eq. 7 against this slot's sample, then the slot's Alg. 2 decision
             float dl = 0.0f;
             if (((same >> j) & 1u) == 0u) dl = delta_l(v.y, v.z, v.w, lab_new);
-            const float W1b = bias_eq7<true>(W1, w, dl);
-            s = W1b + w;
-            take = takes<true>(word, s, W1b);
+            take = decide_eq7(d, word, W1, w, dl, s);
         }
         if (take) {
             tk |= 1u << j;
@@ -962,7 +1012,7 @@ __device__ __forceinline__ uint32_t pixel_per_slot(const FrameDesc& d, uint32_t 
     for (int j = 0; j < K; j += 4)
         st4<kNtWsumSt>(reinterpret_cast<float4*>(wslot + j), make_float4(W[j], W[j + 1], W[j + 2], W[j + 3]));
     if (kResolves && (OP != kIncremental || tk)) {
-        const float rs = resolve_scale<true>(S);
+        const float rs = resolve_scale(d, S);
         float* o = d.out + 3 * (size_t)p;
         st<kNtOut>(o + 0, a0 * rs);
         st<kNtOut>(o + 1, a1 * rs);
@@ -1045,7 +1095,6 @@ union TickShare<true> {
     PerSlotShare<1> slots1;
     PerSlotShare<2> slots2;
     PerSlotShare<4> slots4;
-    PerSlotShare<kWild> wild;
 };
 
 // One wave's share of a lone frame's work item; counts its replaced slots and
@@ -1056,8 +1105,7 @@ __device__ __forceinline__ void tick_item(const FrameDesc& d, uint32_t local, ui
     uint4* list = sh.list;
     if constexpr (PS) {
         if (per_slot_mode(d.bias)) {
-            const uint32_t n = !d.tame     ? per_slot_tile<kWild, kFused>(d, local, wave, sh.wild)
-                               : d.k == 1u ? per_slot_tile<1, kFused>(d, local, wave, sh.slots1)
+            const uint32_t n = d.k == 1u   ? per_slot_tile<1, kFused>(d, local, wave, sh.slots1)
                                : d.k == 2u ? per_slot_tile<2, kFused>(d, local, wave, sh.slots2)
                                : d.k == 4u ? per_slot_tile<4, kFused>(d, local, wave, sh.slots4)
                                            : per_slot_tile<0, kFused>(d, local, wave, sh.slots);
@@ -1070,16 +1118,12 @@ __device__ __forceinline__ void tick_item(const FrameDesc& d, uint32_t local, ui
     n = d.op == kCached ? stream_tiles<KK, kCached, 1>(d, local, wave, list)     \
       : d.op == kFill ? stream_tiles<KK, kFill, 1>(d, local, wave, list)         \
                       : stream_tiles<KK, kFused, 1>(d, local, wave, list)
-    if (!d.tame) {
-        FWRS_TICK_OPS(kWild);
-    } else {
-        switch (d.k) {
-            case 1: FWRS_TICK_OPS(1); break;
-            case 2: FWRS_TICK_OPS(2); break;
-            case 4: FWRS_TICK_OPS(4); break;
-            case 8: FWRS_TICK_OPS(8); break;
-            default: FWRS_TICK_OPS(0); break;
-        }
+    switch (d.k) {
+        case 1: FWRS_TICK_OPS(1); break;
+        case 2: FWRS_TICK_OPS(2); break;
+        case 4: FWRS_TICK_OPS(4); break;
+        case 8: FWRS_TICK_OPS(8); break;
+        default: FWRS_TICK_OPS(0); break;
     }
 #undef FWRS_TICK_OPS
     if (d.stats) add_stats_uniform(d.stats, n);
@@ -1198,21 +1242,19 @@ __global__ __launch_bounds__(64) void tick_fill_kernel(uint32_t* __restrict__ ta
 // (322 with cached stores) = 6.0 TB/s, 1920x1080 k = 8 225 -> 139, Eq. 7 k = 4
 // 141 -> 101, 640x360 14.8 -> 11.0.
 // ---------------------------------------------------------------------------
-template <int SLOTS, bool PER_SLOT>
+template <int K, bool PER_SLOT>
 struct ReprojShare {                            // one wave's pixels
-    static constexpr int kBlocks = SLOTS > 0 ? (SLOTS + 3) / 4 : (kMaxK + 3) / 4;
+    static constexpr int kBlocks = K ? (K + 3) / 4 : (kMaxK + 3) / 4;
     uint4 pixel[64];                            // {p, source, inside | history kept << 1, replaced slots (shared w_sum)}
     float4 colour[64];                          // the new colour, weight; then the resolve
     uint32_t words[PER_SLOT ? 64 : 1][4 * kBlocks];    // Philox words, one per slot (per-slot modes)
 };
 
-template <int SLOTS, bool PER_SLOT>
+template <int K, bool PER_SLOT>
 __device__ __forceinline__ void reproject_tile(const ReprojDesc& r, uint32_t item, uint32_t wave,
-                                               ReprojShare<SLOTS, PER_SLOT>& sh)
+                                               ReprojShare<K, PER_SLOT>& sh)
 {
     const FrameDesc& d = r.f;
-    constexpr bool kTame = SLOTS != kWild;
-    constexpr int K = SLOTS > 0 ? SLOTS : 0;
     constexpr uint32_t D = K == 4 ? 4u : K == 8 ? 2u : 1u;      // rounds loaded ahead
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t kk = K ? (uint32_t)K : d.k;
@@ -1261,23 +1303,18 @@ __device__ __forceinline__ void reproject_tile(const ReprojDesc& r, uint32_t ite
     const float dp = r.src_depth[q];
     const float ws = PER_SLOT ? 0.f : r.src_wsum[q];
     const uint32_t mc = r.src_cnt[q];
-    const float dx = ((float)x + 0.5f) - d.gx;
-    const float dy = ((float)y + 0.5f) - d.gy;
-    const float w = weight_eq4<kTame>(d.c, dx * dx + dy * dy, lv);
     const bool keep = inside && fabsf(dc - dp) <= r.tol * dc;      // NaN (no previous frame) compares false
     const uint32_t m = keep ? mc : 0u;
-    float s = 0.f;
+    float s = 0.f, w;
     uint32_t tk = 0u;
     if constexpr (PER_SLOT) {
+        w = frame_weight(d, x, y, lv);
         for (uint32_t b = 0; 4u * b < kk; ++b) {
             const uint4 t = philox4x32_10(p, d.t, b, d.seed, d.stream_id);
             *reinterpret_cast<uint4*>(&sh.words[lane][4u * b]) = t;
         }
     } else {
-        const float W1b = bias_shared<kTame>(keep ? ws : 0.f, w, d.bias, d.c.decay);
-        s = W1b + w;
-        if constexpr (K > 0) tk = decide_words<K>(philox_words<K>(d, p), W1b, s);
-        else tk = decide_any<kTame>(d, p, W1b, s);
+        tk = decide<K>(d, x, y, p, lv, keep ? ws : 0.f, w, s);
     }
     sh.pixel[lane] = make_uint4(p, q, (in ? 1u : 0u) | (keep ? 2u : 0u), tk);
     sh.colour[lane] = make_float4(c0, c1, c2, w);
@@ -1307,7 +1344,7 @@ __device__ __forceinline__ void reproject_tile(const ReprojDesc& r, uint32_t ite
         } else {
             const uint32_t word = sh.words[e][slot ? j : 0u];
             if (aes) {
-                const float kn = kTame ? div_rn(log2_unit(word), c.w) : log2_unit(word) / c.w;
+                const float kn = aes_key(d, word, c.w);
                 take = kn > Wj;
                 sj = take ? kn : Wj;
             } else {
@@ -1315,9 +1352,7 @@ __device__ __forceinline__ void reproject_tile(const ReprojDesc& r, uint32_t ite
                 float dl = 0.0f;
                 if (!(lab_bounded(c.x, c.y, c.z) && same_colour(t, c.x, c.y, c.z)))
                     dl = delta_l(t.y, t.z, t.w, rgb_to_lab(c.x, c.y, c.z));
-                const float W1j = bias_eq7<kTame>(Wj, c.w, dl);
-                sj = W1j + c.w;
-                take = takes<kTame>(word, sj, W1j);
+                take = decide_eq7(d, word, Wj, c.w, dl, sj);
             }
         }
         const bool own = slot && (px.z & 1u) != 0u;
@@ -1326,12 +1361,13 @@ __device__ __forceinline__ void reproject_tile(const ReprojDesc& r, uint32_t ite
             t = make_float4(c.w, c.x, c.y, c.z);
             ti = d.t;
         }
+        if (!slot) t = make_float4(0.f, 0.f, 0.f, 0.f);
         const uint64_t took = __ballot(take);
         slots += (uint32_t)__builtin_popcountll(took);
         const bool any = ((took >> (lane & ~((1u << lg) - 1u))) & ((1ull << (1u << lg)) - 1ull)) != 0u;
         changed += (uint32_t)__builtin_popcountll(__ballot(any && j == 0u));
         if (d.out) {                                    // uniform
-            const float rs = resolve_scale<kTame>(group_sum<K>(t.x, kk));
+            const float rs = resolve_scale(d, group_sum<K>(t.x, kk));
             const float q0 = group_sum<K>(t.x * t.y, kk) * rs;
             const float q1 = group_sum<K>(t.x * t.z, kk) * rs;
             const float q2 = group_sum<K>(t.x * t.w, kk) * rs;
@@ -1675,15 +1711,11 @@ __global__ void fill_u32_kernel(uint32_t* __restrict__ p, size_t n, uint32_t v)
 // ---------------------------------------------------------------------------
 // Host-side launchers.
 // ---------------------------------------------------------------------------
-// The per-pixel code's slot-count argument for a frame.
-static int slots_arg(const FrameDesc& d) { return d.tame ? (int)d.k : kWild; }
-
 template <int OP, int T>
 static hipError_t launch_shared(const FrameDesc& d, hipStream_t stream)
 {
     const dim3 grid((d.items + (uint32_t)T - 1u) / (uint32_t)T), block(kBlock);
-    switch (slots_arg(d)) {
-        case kWild: hipLaunchKernelGGL((frame_kernel<kWild, OP, false, T>), grid, block, 0, stream, d); break;
+    switch (d.k) {
         case 1: hipLaunchKernelGGL((frame_kernel<1, OP, false, T>), grid, block, 0, stream, d); break;
         case 2: hipLaunchKernelGGL((frame_kernel<2, OP, false, T>), grid, block, 0, stream, d); break;
         case 4: hipLaunchKernelGGL((frame_kernel<4, OP, false, T>), grid, block, 0, stream, d); break;
@@ -1697,8 +1729,7 @@ template <int OP, int T>
 static void launch_per_slot(const FrameDesc& d, hipStream_t stream)
 {
     const dim3 grid(d.items), block(kBlock);
-    switch (slots_arg(d)) {
-        case kWild: hipLaunchKernelGGL((frame_kernel<kWild, OP, true, T>), grid, block, 0, stream, d); break;
+    switch (d.k) {
         case 1: hipLaunchKernelGGL((frame_kernel<1, OP, true, T>), grid, block, 0, stream, d); break;
         case 2: hipLaunchKernelGGL((frame_kernel<2, OP, true, T>), grid, block, 0, stream, d); break;
         case 4: hipLaunchKernelGGL((frame_kernel<4, OP, true, T>), grid, block, 0, stream, d); break;
@@ -1715,8 +1746,8 @@ static hipError_t launch_frame_op(const FrameDesc& d, hipStream_t stream)
         if (per_slot_mode(d.bias)) {
             const dim3 grid(d.items), block(kBlock);
             if (store_streams(d)) launch_per_slot<OP, 2>(d, stream);
-            else if (d.tame && d.k == 4u) hipLaunchKernelGGL((frame_kernel<4, OP, true, 0>), grid, block, 0, stream, d);
-            else if (d.tame && d.k == 8u) hipLaunchKernelGGL((frame_kernel<8, OP, true, 0>), grid, block, 0, stream, d);
+            else if (d.k == 4u) hipLaunchKernelGGL((frame_kernel<4, OP, true, 0>), grid, block, 0, stream, d);
+            else if (d.k == 8u) hipLaunchKernelGGL((frame_kernel<8, OP, true, 0>), grid, block, 0, stream, d);
             else launch_per_slot<OP, 1>(d, stream);
             return hipGetLastError();
         }
@@ -1766,11 +1797,7 @@ hipError_t launch_reproject(const ReprojDesc& r, hipStream_t stream)
 {
     const dim3 grid(r.f.items), block(kBlock);
     const bool eq7 = per_slot_mode(r.f.bias);
-    switch (slots_arg(r.f)) {
-        case kWild:
-            if (eq7) hipLaunchKernelGGL((reproject_kernel<kWild, true>), grid, block, 0, stream, r);
-            else hipLaunchKernelGGL((reproject_kernel<kWild, false>), grid, block, 0, stream, r);
-            break;
+    switch (r.f.k) {
         case 1:
             if (eq7) hipLaunchKernelGGL((reproject_kernel<1, true>), grid, block, 0, stream, r);
             else hipLaunchKernelGGL((reproject_kernel<1, false>), grid, block, 0, stream, r);
@@ -1864,10 +1891,7 @@ hipError_t launch_foveated(const FovDesc& fd, int op, hipStream_t stream)
     } while (0)
     if (ps) {
         const bool push = op == kPush;
-        if (!fd.f.tame) {
-            if (push) FWRS_FOV_LAUNCH(kWild, true, kPush);
-            else FWRS_FOV_LAUNCH(kWild, true, kFused);
-        } else if (fd.f.k == 1) {
+        if (fd.f.k == 1) {
             if (push) FWRS_FOV_LAUNCH(1, true, kPush);
             else FWRS_FOV_LAUNCH(1, true, kFused);
         } else if (fd.f.k == 2) {
@@ -1886,8 +1910,7 @@ hipError_t launch_foveated(const FovDesc& fd, int op, hipStream_t stream)
             else FWRS_FOV_LAUNCH(0, true, kFused);
         }
     } else {
-        switch (slots_arg(fd.f)) {
-            case kWild: FWRS_FOV_OPS(kWild); break;
+        switch (fd.f.k) {
             case 4: FWRS_FOV_OPS(4); break;
             case 8: FWRS_FOV_OPS(8); break;
             default: FWRS_FOV_OPS(0); break;
