@@ -456,14 +456,13 @@ __device__ __forceinline__ void add_stats(unsigned long long* stats, uint32_t v)
 // ---------------------------------------------------------------------------
 // A frame of a mode with one w_sum per pixel: T tiles of 64 pixels per wave.
 //  1. One lane per pixel: the loads every pixel needs (level, w_sum, for kCached
-//     its resolve from the plane), then the decision.  The pixels whose record is
-//     needed -- those that replace a slot, or all of them where every resolve is
-//     taken from the records (kFused, kFill, kResolve) -- go on a list in LDS.
+//     its resolve from the plane), then the decision.  The pixels that replace a
+//     slot go on a list in LDS.
 //  2. One lane per slot: groups of lanes work through the list, so a record
 //     (16k bytes) is one coalesced access instead of k accesses 16k bytes apart,
 //     and a wave holds only pixels that have work.
-//  3. One lane per pixel: w_sum and the output row, a listed pixel's resolve read
-//     back from the list, so rows leave whole.
+//  3. One lane per pixel: w_sum and (kCached) the output row, a listed pixel's
+//     resolve read back from the list, so rows leave whole.
 // The list is the wave's own, so no barrier is needed.  Stores come after the
 // loads of the same step, because vector-memory operations are waited for in
 // order.
@@ -545,20 +544,16 @@ __device__ __forceinline__ float group_sum(float v, uint32_t kk)
 }
 
 // The list's n pixels: entry {x, y, weight, replaced slots | level << 16}.  A
-// group of lanes takes a pixel, 64 / group pixels a round.  Replaced slots are
-// stored; where most pixels of a frame replace slots (kFused, kFill) a pixel that
-// replaces at least a quarter stores its whole record, because full lines are
-// written faster than parts of them (k = 8 while filling 108.9 -> 106.1 us a
-// 1920x1080 frame, k = 4 at 3840x2160 258 -> 250.6; 6% slower for kCached, whose
-// changed pixels are few).  The resolve goes to the list, for kCached also to the
-// plane; kIncremental writes the output here.  Returns the lane's replaced slots.
-// (Loading 2, 4 or 8 rounds ahead of the first: within 1% at 2, slower beyond,
-// for the registers.)
+// group of lanes takes a pixel, 64 / group pixels a round.  Kept slots are read,
+// replaced slots stored (whole records, as whole_tile has them: 6% slower here, where
+// few pixels change).  The resolve goes to the list and the plane (kCached) or to
+// the output (kIncremental).  Returns the lane's replaced slots.  (Loading 2, 4 or 8
+// rounds ahead of the first: within 1% at 2, slower beyond, for the registers.)
 template <int K, int OP, bool FOV, bool TAME>
 __device__ __forceinline__ uint32_t listed_pixels(const FrameDesc& d, const FovSrc* fs, uint4* list, uint32_t n)
 {
-    constexpr bool kResolves = OP != kPush, kUpdates = OP != kResolve;
-    constexpr bool kWhole = OP == kFused || OP == kFill;
+    static_assert(OP == kPush || OP == kIncremental || OP == kCached, "the ops that need few records");
+    constexpr bool kResolves = OP != kPush;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t kk = K ? (uint32_t)K : d.k;
     const uint32_t lg = group_log2<K>(kk), first = group_first<K>(kk);
@@ -572,36 +567,32 @@ __device__ __forceinline__ uint32_t listed_pixels(const FrameDesc& d, const FovS
         const uint4 entry = list[own ? at : b];     // past the end: an entry no result has replaced yet
         const uint32_t p = entry.y * d.width + entry.x;
         const size_t s = (size_t)p * kk + (slot ? j : 0u);
+        const bool take = slot && ((entry.w >> j) & 1u) != 0u;
         float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (kResolves && !empty) r = ld4<kNtRecLd>(reinterpret_cast<const float4*>(d.rec) + s);
-        if (!slot) r = make_float4(0.f, 0.f, 0.f, 0.f);
-        bool take = false;
-        if constexpr (kUpdates) {
-            float c0, c1, c2;
-            if constexpr (K == 1 || K == 2) {
-                if constexpr (FOV) {
-                    const float3 c = fov_colour(*fs, entry.x, entry.y, p, entry.w >> 16);
-                    c0 = c.x;
-                    c1 = c.y;
-                    c2 = c.z;
-                } else {
-                    const float* color = d.color + 3 * (size_t)p;
-                    c0 = ld<kNtColor>(color + 0);
-                    c1 = ld<kNtColor>(color + 1);
-                    c2 = ld<kNtColor>(color + 2);
-                }
-            } else {                                // each lane of a quad loads one channel
-                const uint32_t ch = (j & 3u) < 3u ? (j & 3u) : 2u;
-                float c;
-                if constexpr (FOV) c = fov_channel(*fs, entry.x, entry.y, p, entry.w >> 16, ch);
-                else c = ld<kNtColor>(d.color + 3 * (size_t)p + ch);
-                c0 = quad_perm<0, 0, 0, 0>(c);
-                c1 = quad_perm<1, 1, 1, 1>(c);
-                c2 = quad_perm<2, 2, 2, 2>(c);
+        if (kResolves && !empty && slot && !take) r = ld4<kNtRecLd>(reinterpret_cast<const float4*>(d.rec) + s);
+        float c0, c1, c2;
+        if constexpr (K == 1 || K == 2) {
+            if constexpr (FOV) {
+                const float3 c = fov_colour(*fs, entry.x, entry.y, p, entry.w >> 16);
+                c0 = c.x;
+                c1 = c.y;
+                c2 = c.z;
+            } else {
+                const float* color = d.color + 3 * (size_t)p;
+                c0 = ld<kNtColor>(color + 0);
+                c1 = ld<kNtColor>(color + 1);
+                c2 = ld<kNtColor>(color + 2);
             }
-            take = slot && ((entry.w >> j) & 1u) != 0u;
-            if (take) r = make_float4(__builtin_bit_cast(float, entry.z), c0, c1, c2);
+        } else {                                    // each lane of a quad loads one channel
+            const uint32_t ch = (j & 3u) < 3u ? (j & 3u) : 2u;
+            float c;
+            if constexpr (FOV) c = fov_channel(*fs, entry.x, entry.y, p, entry.w >> 16, ch);
+            else c = ld<kNtColor>(d.color + 3 * (size_t)p + ch);
+            c0 = quad_perm<0, 0, 0, 0>(c);
+            c1 = quad_perm<1, 1, 1, 1>(c);
+            c2 = quad_perm<2, 2, 2, 2>(c);
         }
+        if (take) r = make_float4(__builtin_bit_cast(float, entry.z), c0, c1, c2);
         float q0 = 0.f, q1 = 0.f, q2 = 0.f;
         if constexpr (kResolves) {
             const float rs = resolve_scale_as<TAME>(group_sum<K>(r.x, kk));
@@ -610,13 +601,12 @@ __device__ __forceinline__ uint32_t listed_pixels(const FrameDesc& d, const FovS
             q2 = group_sum<K>(r.x * r.w, kk) * rs;
         }
         if (own) {
-            const bool whole = kWhole && slot && 4u * (uint32_t)__popc(entry.w & 0xFFFFu) >= kk;
-            if (take || whole) st4<kNtRecSt>(reinterpret_cast<float4*>(d.rec) + s, r);
             if (take) {
+                st4<kNtRecSt>(reinterpret_cast<float4*>(d.rec) + s, r);
                 st<kNtIdxSt>(d.idx + s, d.t);
                 taken += 1u;
             }
-            if constexpr (OP == kCached || OP == kIncremental) {
+            if constexpr (kResolves) {
                 float* to = (OP == kCached ? d.res : d.out) + 3 * (size_t)p;
                 constexpr uint32_t bit = OP == kCached ? kNtResSt : 0u;    // scattered: never non-temporal
                 if constexpr (K == 1 || K == 2) {
@@ -629,7 +619,7 @@ __device__ __forceinline__ uint32_t listed_pixels(const FrameDesc& d, const FovS
                     st<bit>(to + (j - first), j == first ? q0 : j == first + 1u ? q1 : q2);
                 }
             }
-            if (kResolves && OP != kIncremental && j == first)
+            if (OP == kCached && j == first)
                 list[at] = make_uint4(__builtin_bit_cast(uint32_t, q0), __builtin_bit_cast(uint32_t, q1),
                                       __builtin_bit_cast(uint32_t, q2), 0u);
         }
@@ -643,9 +633,6 @@ template <int K, int OP, int T, bool FOV = false>
 __device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t item0, uint32_t wave, uint4* list,
                                                  const FovSrc* fs = nullptr)
 {
-    constexpr bool kUpdates = OP != kResolve;
-    constexpr bool kAll = OP == kFused || OP == kFill || OP == kResolve;    // every pixel is listed
-    constexpr bool kRow = OP == kCached || kAll;                            // the output leaves by rows
     const uint32_t lane = threadIdx.x & 63u;
 
     uint32_t x[T], y[T], p[T], lv[T], at[T];
@@ -655,12 +642,9 @@ __device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t it
     for (int t = 0; t < T; ++t) {
         in[t] = item_pixel_of(d, item0 + t, wave, lane, x[t], y[t]);
         p[t] = in[t] ? y[t] * d.width + x[t] : 0u;          // lanes outside read pixel 0 and store nothing
-        lv[t] = 0u;
-        if constexpr (kUpdates) {
-            if constexpr (FOV) lv[t] = fov_level(*fs, d.gx, d.gy, x[t], y[t]);
-            else lv[t] = ld<kNtLevel>(d.level + p[t]);
-            W[t] = ld<kNtWsumLd>(d.wsum + p[t]);
-        }
+        if constexpr (FOV) lv[t] = fov_level(*fs, d.gx, d.gy, x[t], y[t]);
+        else lv[t] = ld<kNtLevel>(d.level + p[t]);
+        W[t] = ld<kNtWsumLd>(d.wsum + p[t]);
         if constexpr (OP == kCached) {
             const float* res = d.res + 3 * (size_t)p[t];
             q0[t] = ld<kNtResLd>(res + 0);
@@ -668,39 +652,34 @@ __device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t it
             q2[t] = ld<kNtResLd>(res + 2);
         }
     }
-    uint32_t n = 0u, changed = 0u;
+    uint32_t n = 0u;
 #pragma unroll
     for (int t = 0; t < T; ++t) {
-        uint32_t tk = 0u;
-        float w = 0.f;
-        if constexpr (kUpdates) {
-            float s;
-            tk = decide<K>(d, x[t], y[t], p[t], lv[t], W[t], w, s);
-            if (!in[t]) tk = 0u;
-            W[t] = s;
-        }
-        const uint64_t took = __ballot(tk != 0u), mask = kAll ? __ballot(in[t]) : took;
-        changed += (uint32_t)__builtin_popcountll(took);
-        at[t] = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-        if (kAll ? in[t] : tk != 0u)
+        float w, s;
+        uint32_t tk = decide<K>(d, x[t], y[t], p[t], lv[t], W[t], w, s);
+        if (!in[t]) tk = 0u;
+        W[t] = s;
+        const uint64_t took = __ballot(tk != 0u);
+        at[t] = 0xFFFFFFFFu;
+        if (tk) {
+            at[t] = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(took >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)took, 0u));
             list[at[t]] = make_uint4(x[t], y[t], __builtin_bit_cast(uint32_t, w), tk | (lv[t] << 16));
-        else
-            at[t] = 0xFFFFFFFFu;
-        n += (uint32_t)__builtin_popcountll(mask);
+        }
+        n += (uint32_t)__builtin_popcountll(took);
     }
     wave_lds_fence();
     uint32_t slots = 0u;
     if (n) {
         if (OP == kPush || d.tame) slots = listed_pixels<K, OP, FOV, true>(d, fs, list, n);
         else slots = listed_pixels<K, OP, FOV, false>(d, fs, list, n);
+        slots = wave_sum(slots);
     }
-    if (changed) slots = wave_sum(slots);
     wave_lds_fence();
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         if (!in[t]) continue;
-        if constexpr (kUpdates) st<kNtWsumSt>(d.wsum + p[t], W[t]);
-        if constexpr (kRow) {
+        st<kNtWsumSt>(d.wsum + p[t], W[t]);
+        if constexpr (OP == kCached) {
             if (at[t] != 0xFFFFFFFFu) {
                 const uint4 v = list[at[t]];
                 q0[t] = __builtin_bit_cast(float, v.x);
@@ -711,12 +690,162 @@ __device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t it
             st<kNtOut>(o + 0, q0[t]);
             st<kNtOut>(o + 1, q1[t]);
             st<kNtOut>(o + 2, q2[t]);
-            if constexpr (OP == kFill) {
-                float* res = d.res + 3 * (size_t)p[t];
-                st<kNtResSt>(res + 0, q0[t]);
-                st<kNtResSt>(res + 1, q1[t]);
-                st<kNtResSt>(res + 2, q2[t]);
+        }
+    }
+    return slots + (n << 16);
+}
+
+// ---------------------------------------------------------------------------
+// The ops that take every pixel's resolve from its record (kFused, kFill; kResolve
+// for a run-time slot count), 64 pixels a wave: no list is needed, so the first
+// rounds' records are loaded with the pixels' own inputs, ahead of the decisions,
+// and the colours, of the pixels that replace a slot, with one lane per pixel.
+// Where many pixels replace slots, whole records are stored (below).  Against
+// the list with every pixel on it, whose rounds each wait for a record and a
+// colour: while a store fills 53 -> 45 us at 1280x720, k = 8, and 96.5 -> 94 at
+// 2560x1440, k = 4; without a resolve plane at frame 600 37.5 -> 36.2 at 1920x1080,
+// k = 4, and 332 -> 315 at 3840x2160, k = 8 (one lane per pixel with its k loads:
+// 62, 120, 35.8 and 317).  Rounds loaded ahead: at k = 4 two (four: 28 us against
+// 26.5 at 1280x720 while filling), at k = 8 one (two: 28.8 against 27.2 at frame 600).
+// ---------------------------------------------------------------------------
+// kResolve at a compiled slot count: one lane per pixel, its record in registers (the
+// rounds of whole_tile: 188 us against 202 at 3840x2160, k = 8).
+template <int K>
+__device__ __forceinline__ void resolve_pixel(const FrameDesc& d, uint32_t item, uint32_t wave)
+{
+    uint32_t x, y;
+    if (!item_pixel_of(d, item, wave, threadIdx.x & 63u, x, y)) return;
+    const uint32_t p = y * d.width + x;
+    const float4* rec = reinterpret_cast<const float4*>(d.rec) + (size_t)p * K;
+    float4 r[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) r[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (d.t != 0u) {                            // the empty store: every slot zero, nothing to read
+#pragma unroll
+        for (int j = 0; j < K; ++j) r[j] = ld4<kNtRecLd>(rec + j);
+    }
+    float q0, q1, q2;
+    resolve_slots<K>(d, r, q0, q1, q2);
+    float* o = d.out + 3 * (size_t)p;
+    st<kNtOut>(o + 0, q0);
+    st<kNtOut>(o + 1, q1);
+    st<kNtOut>(o + 2, q2);
+}
+
+struct WholeShare {                             // one wave's pixels
+    uint2 pixel[64];                            // {p, inside | replaced slots << 1}
+    float4 colour[64];                          // the new colour, weight; then the resolve
+};
+
+template <int K, int OP, bool FOV = false>
+__device__ __forceinline__ uint32_t whole_tile(const FrameDesc& d, uint32_t item, uint32_t wave, WholeShare& sh,
+                                               const FovSrc* fs = nullptr)
+{
+    static_assert(OP == kFused || OP == kFill || OP == kResolve, "the ops that read every record");
+    constexpr bool kUpdates = OP != kResolve;
+    constexpr uint32_t D = K == 0 || K == 2 || K == 4 ? 2u : 1u;    // rounds loaded ahead
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t kk = K ? (uint32_t)K : d.k;
+    const uint32_t lg = group_log2<K>(kk), first = group_first<K>(kk);
+    const uint32_t j = lane & ((1u << lg) - 1u), per = 64u >> lg;
+    const bool slot = K || j < kk;
+    const bool empty = d.t == 0u;               // frame 0 meets the empty store: nothing to read
+
+    uint32_t x, y;
+    const bool in = item_pixel_of(d, item, wave, lane, x, y);
+    const uint32_t p = in ? y * d.width + x : 0u;           // lanes outside read pixel 0 and store nothing
+    sh.pixel[lane] = make_uint2(p, in ? 1u : 0u);
+    uint32_t lv = 0u;
+    float W = 0.f;
+    if constexpr (kUpdates) {
+        if constexpr (FOV) lv = fov_level(*fs, d.gx, d.gy, x, y);
+        else lv = ld<kNtLevel>(d.level + p);
+        W = ld<kNtWsumLd>(d.wsum + p);
+    }
+    wave_lds_fence();
+    float4 v[D];
+    auto load = [&](uint32_t b) {
+        const size_t at = (size_t)sh.pixel[b + (lane >> lg)].x * kk + (slot ? j : 0u);
+        return ld4<kNtRecLd>(reinterpret_cast<const float4*>(d.rec) + at);
+    };
+#pragma unroll
+    for (uint32_t u = 0; u < D; ++u) {
+        v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (u * per < 64u && !empty) v[u] = load(u * per);
+    }
+    uint32_t slots = 0u, changed = 0u;
+    if constexpr (kUpdates) {
+        float w, s;
+        uint32_t tk = decide<K>(d, x, y, p, lv, W, w, s);
+        if (!in) tk = 0u;
+        W = s;
+        changed = (uint32_t)__builtin_popcountll(__ballot(tk != 0u));
+        if (changed) slots = wave_sum((uint32_t)__popc(tk));
+        if (tk) {
+            float c0, c1, c2;
+            if constexpr (FOV) {
+                const float3 c = fov_colour(*fs, x, y, p, lv);
+                c0 = c.x;
+                c1 = c.y;
+                c2 = c.z;
+            } else {
+                const float* color = d.color + 3 * (size_t)p;
+                c0 = ld<kNtColor>(color + 0);
+                c1 = ld<kNtColor>(color + 1);
+                c2 = ld<kNtColor>(color + 2);
             }
+            sh.pixel[lane] = make_uint2(p, 1u | (tk << 1));
+            sh.colour[lane] = make_float4(c0, c1, c2, w);
+        }
+        wave_lds_fence();
+    }
+
+    // one lane per slot
+    for (uint32_t b0 = 0; b0 < 64u; b0 += D * per)
+#pragma unroll
+    for (uint32_t u = 0; u < D; ++u) {
+        const uint32_t b = b0 + u * per;
+        if (b >= 64u) break;
+        const uint32_t e = b + (lane >> lg);
+        const uint2 px = sh.pixel[e];
+        float4 r = v[u];
+        if (b + D * per < 64u && !empty) v[u] = load(b + D * per);
+        bool take = false;
+        if constexpr (kUpdates) {
+            take = slot && ((px.y >> (1u + j)) & 1u) != 0u;
+            if (take) {
+                const float4 c = sh.colour[e];
+                r = make_float4(c.w, c.x, c.y, c.z);
+            }
+        }
+        if (!slot) r = make_float4(0.f, 0.f, 0.f, 0.f);
+        const float rs = resolve_scale(d, group_sum<K>(r.x, kk));
+        const float q0 = group_sum<K>(r.x * r.y, kk) * rs;
+        const float q1 = group_sum<K>(r.x * r.z, kk) * rs;
+        const float q2 = group_sum<K>(r.x * r.w, kk) * rs;
+        if constexpr (kUpdates) {
+            const size_t at = (size_t)px.x * kk + (slot ? j : 0u);
+            // full lines are written faster than parts of them (k = 8 while filling 108.9
+            // -> 106.1 us a 1920x1080 frame, k = 4 at 3840x2160 258 -> 250.6)
+            const bool whole = slot && 4u * (uint32_t)__popc(px.y >> 1) >= kk;
+            if (take || whole) st4<kNtRecSt>(reinterpret_cast<float4*>(d.rec) + at, r);
+            if (take) st<kNtIdxSt>(d.idx + at, d.t);
+        }
+        if (j == first) sh.colour[e] = make_float4(q0, q1, q2, 0.f);
+    }
+    wave_lds_fence();
+    if (in) {
+        if constexpr (kUpdates) st<kNtWsumSt>(d.wsum + p, W);
+        const float4 q = sh.colour[lane];
+        float* o = d.out + 3 * (size_t)p;
+        st<kNtOut>(o + 0, q.x);
+        st<kNtOut>(o + 1, q.y);
+        st<kNtOut>(o + 2, q.z);
+        if constexpr (OP == kFill) {
+            float* res = d.res + 3 * (size_t)p;
+            st<kNtResSt>(res + 0, q.x);
+            st<kNtResSt>(res + 1, q.y);
+            st<kNtResSt>(res + 2, q.z);
         }
     }
     return slots + (changed << 16);
@@ -1045,18 +1174,32 @@ __device__ __forceinline__ void frame_block(const FrameDesc& d, uint32_t block, 
         __shared__ PerSlotShare<K> share[kBlock / 64];
         const uint32_t n = per_slot_tile<K, OP, FOV, T == 2>(d, block, wave, share[wave], fs);
         if (d.stats) add_stats_uniform(d.stats, n);
+    } else if constexpr (OP == kResolve && K > 0) {
+        resolve_pixel<K>(d, block, wave);
+    } else if constexpr (OP == kFused || OP == kFill || OP == kResolve) {
+        __shared__ WholeShare share[kBlock / 64];
+        const uint32_t n = whole_tile<K, OP, FOV>(d, block, wave, share[wave], fs);
+        if (OP != kResolve && d.stats) add_stats_uniform(d.stats, n);
     } else {
         __shared__ uint4 list[kBlock / 64][64 * T];
         const uint32_t n = stream_tiles<K, OP, T, FOV>(d, T * block, wave, list[wave], fs);
-        if (OP != kResolve && d.stats) add_stats_uniform(d.stats, n);
+        if (d.stats) add_stats_uniform(d.stats, n);
     }
 }
 
 // Waves per SIMD the frame kernels are compiled for (T = 0: no bound).
 constexpr int kFrameWaves = 8;
 
+// ... and the most they run with: resolve_pixel reads a record in k accesses, which
+// eight waves a SIMD push out of L1 between the first and the last (3840x2160, k = 8:
+// 213 us with 8 waves, 191 with 6, 188 with 4, 216 with 2; k = 4 107, 106, 103 and
+// 110; k = 2 49.5, 50.7, 52.5 and 69).
+constexpr int frame_waves(int k, int op, int t) { return op == kResolve && k >= 4 ? 4 : t ? kFrameWaves : 1; }
+constexpr int frame_waves_most(int k, int op) { return op == kResolve && k >= 4 ? 4 : 8; }
+
 template <int K, int OP, bool PER_SLOT = false, int T = 1>
-__global__ __launch_bounds__(kBlock, T ? kFrameWaves : 1) void frame_kernel(FrameDesc d)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(frame_waves(K, OP, T), frame_waves_most(K, OP))))
+void frame_kernel(FrameDesc d)
 {
     frame_block<K, OP, PER_SLOT, T, false>(d, frame_item(blockIdx.x, gridDim.x, d.t), nullptr);
 }
@@ -1087,10 +1230,12 @@ __global__ __launch_bounds__(kBlock, T ? kFrameWaves : 1) void frame_kernel(Fram
 template <bool PS>
 union TickShare {
     uint4 list[64];
+    WholeShare whole;
 };
 template <>
 union TickShare<true> {
     uint4 list[64];
+    WholeShare whole;
     PerSlotShare<0> slots;
     PerSlotShare<1> slots1;
     PerSlotShare<2> slots2;
@@ -1102,7 +1247,6 @@ union TickShare<true> {
 template <bool PS>
 __device__ __forceinline__ void tick_item(const FrameDesc& d, uint32_t local, uint32_t wave, TickShare<PS>& sh)
 {
-    uint4* list = sh.list;
     if constexpr (PS) {
         if (per_slot_mode(d.bias)) {
             const uint32_t n = d.k == 1u   ? per_slot_tile<1, kFused>(d, local, wave, sh.slots1)
@@ -1115,9 +1259,9 @@ __device__ __forceinline__ void tick_item(const FrameDesc& d, uint32_t local, ui
     }
     uint32_t n = 0u;
 #define FWRS_TICK_OPS(KK)                                                        \
-    n = d.op == kCached ? stream_tiles<KK, kCached, 1>(d, local, wave, list)     \
-      : d.op == kFill ? stream_tiles<KK, kFill, 1>(d, local, wave, list)         \
-                      : stream_tiles<KK, kFused, 1>(d, local, wave, list)
+    n = d.op == kCached ? stream_tiles<KK, kCached, 1>(d, local, wave, sh.list)  \
+      : d.op == kFill ? whole_tile<KK, kFill>(d, local, wave, sh.whole)          \
+                      : whole_tile<KK, kFused>(d, local, wave, sh.whole)
     switch (d.k) {
         case 1: FWRS_TICK_OPS(1); break;
         case 2: FWRS_TICK_OPS(2); break;
