@@ -30,7 +30,7 @@ constexpr int kDefaultTileX = 64, kDefaultTileY = 1;
 // store fills (the first frames after a reset), most pixels replace a slot every
 // frame, so copying unchanged resolves from the plane saves little and keeping
 // the plane costs a write per changed pixel; the frame before this one writes the
-// plane densely (kOpFill) and later frames use it (kOpCached).  A launch-policy
+// plane densely (kOpFill) and later frames use it (kOpCached, kOpCachedNt).  A launch-policy
 // constant: it never changes results.
 #ifndef FWRS_RES_FROM
 #define FWRS_RES_FROM 32
@@ -286,25 +286,29 @@ FrameDesc make_desc(const fwrs_ctx* x, const float* color, const uint8_t* level,
 
 bool gaze_ok(float gx, float gy) { return std::isfinite(gx) && std::isfinite(gy); }
 
+// The bytes of x's slot records.
+uint64_t record_bytes(const fwrs_ctx* x) { return (uint64_t)x->width * (uint64_t)x->height * (uint64_t)x->k * 16u; }
+
 // The kernel op of a fused frame (update + resolve of every pixel) of context x
 // at frame index t with the resolve plane valid or not (res_valid): from the
 // resolve plane once it is valid and the store is past its filling frames,
-// filling the plane on the frame before.
-int fused_op_at(const fwrs_ctx* x, uint32_t t, bool res_valid)
+// filling the plane on the frame before.  `records`: the bytes of the slot records
+// that the launch goes through (x's, in a batched tick all its contexts').
+int fused_op_at(const fwrs_ctx* x, uint32_t t, bool res_valid, uint64_t records)
 {
     if (!x->res) return fwrs::kOpFused;
-    if (res_valid && t >= x->res_from) return fwrs::kOpCached;
+    if (res_valid && t >= x->res_from) return records <= fwrs::kCacheBytes ? fwrs::kOpCachedNt : fwrs::kOpCached;
     return t + 1u >= x->res_from ? fwrs::kOpFill : fwrs::kOpFused;
 }
 
-int fused_op(const fwrs_ctx* x) { return fused_op_at(x, x->t, x->res_valid); }
+int fused_op(const fwrs_ctx* x) { return fused_op_at(x, x->t, x->res_valid, record_bytes(x)); }
 
 // Whether the plane holds every pixel's resolve after a frame run as `op` on x.
 bool plane_after(const fwrs_ctx* x, int op)
 {
     // kOpPush, kOpFused and kOpIncremental change records without the plane;
     // a group leaves it whole wherever it is kept
-    return op == fwrs::kOpCached || op == fwrs::kOpFill || (op == fwrs::kOpGroup && x->res);
+    return op == fwrs::kOpCached || op == fwrs::kOpCachedNt || op == fwrs::kOpFill || (op == fwrs::kOpGroup && x->res);
 }
 
 // After a successful launch of `op` on x at a gaze: the frame count, the record
@@ -782,9 +786,11 @@ int layout_tick(const fwrs_frame* frames, int n, bool reverse, TileFn tile, Tick
     bool per_slot = false;
     const uint64_t mark = g_tick_marks.fetch_add(1u, std::memory_order_relaxed) + 1u;
     int groups = 0;
+    uint64_t records = 0;
     for (int i = 0; i < n; ++i) {
         fwrs_ctx* x = frames[i].ctx;
         if (x->tick_mark != mark) {
+            records += record_bytes(x);
             x->tick_mark = mark;
             x->tick_group = groups;
             w.count[groups] = 0;
@@ -816,7 +822,7 @@ int layout_tick(const fwrs_frame* frames, int n, bool reverse, TileFn tile, Tick
         d.t = x->t + (uint32_t)at;
         const bool plane = (w.plane[g] & 1) != 0;
         const bool tame = tame_at(x, (w.plane[g] & 2) != 0, f.gaze_x, f.gaze_y);
-        const int op = nf > 1 && group_kernel(x) ? fwrs::kOpGroup : fused_op_at(x, d.t, plane);
+        const int op = nf > 1 && group_kernel(x) ? fwrs::kOpGroup : fused_op_at(x, d.t, plane, records);
         w.plane[g] = (plane_after(x, op) ? 1 : 0) | (tame ? 2 : 0);
         d.tame = tame ? 1u : 0u;
         if (nf > 1 && groups_kind != fwrs::kTickGroups8)

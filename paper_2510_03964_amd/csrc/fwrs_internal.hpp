@@ -21,9 +21,13 @@ constexpr int kOpResolve = 2;       // resolve only
 constexpr int kOpFused = 3;         // update + resolve of every pixel from its slots
 constexpr int kOpIncremental = 5;   // update + resolve of the changed pixels only
 constexpr int kOpCached = 7;        // update + resolve, unchanged pixels from the resolve plane
+constexpr int kOpCachedNt = 8;      // kOpCached for stores that fit the Infinity Cache (kCacheBytes)
 constexpr int kOpFill = 9;          // kOpFused that also writes the resolve plane
 constexpr int kOpGroup = 11;        // batched ticks: a group's frames with the pixel state held in registers
 hipError_t launch_frame(const FrameDesc& d, int op, hipStream_t stream);
+
+// The Infinity Cache, for the rules that ask whether a launch's slot records fit it.
+constexpr uint64_t kCacheBytes = 256ull << 20;
 
 // A batched tick's table in device memory: this head, then (at kTickDescOffset)
 // the n group leaders' descriptors in the order their work items are numbered

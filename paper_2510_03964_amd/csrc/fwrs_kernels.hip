@@ -30,12 +30,8 @@
 
 // Which streams use non-temporal loads / stores (bits, see kNt* below); a
 // launch-shape tuning constant that never changes results.  Level, colour,
-// w_sum and the output are streamed once a frame.  The resolve plane is not
-// among them: a changed pixel rewrites 12 bytes of a line that was just read,
-// and non-temporal partial stores go to memory one by one (scattered 12-byte
-// stores of 8% of the pixels: 22 us against 14).  Three 3840x2160 sessions in
-// turn, frame 60: 224 us with the plane non-temporal, 211 without, 233 with
-// nothing non-temporal; the stereo pair at k = 8 454, 422 and 448.
+// w_sum and the output are streamed once a frame.  The resolve plane is a choice of
+// the op (kCachedNt), the incremental output's scattered stores one of scattered_nt.
 #ifndef FWRS_NT_MASK
 #define FWRS_NT_MASK 0x0C7u
 #endif
@@ -48,11 +44,11 @@ namespace fwrs {
 // else); kCached: update + resolve of every pixel, where a pixel without a
 // replacement copies its resolve from the store's resolve plane (which holds it
 // unchanged since the pixel last changed) and a changed pixel recomputes it and
-// refreshes the plane; kFill: kFused that also writes every pixel's resolve into
+// refreshes the plane; kCachedNt: kCached with non-temporal accesses to the plane; kFill: kFused that also writes every pixel's resolve into
 // the plane, making it valid for the kCached frames that follow.
 enum Op : int {
     kPush = kOpPush, kResolve = kOpResolve, kFused = kOpFused, kIncremental = kOpIncremental, kCached = kOpCached,
-    kFill = kOpFill, kGroup = kOpGroup,
+    kCachedNt = kOpCachedNt, kFill = kOpFill, kGroup = kOpGroup,
 };
 
 enum : uint32_t {
@@ -93,6 +89,21 @@ template <uint32_t BIT, typename T>
 __device__ __forceinline__ void st(T* p, T v)
 {
     if constexpr ((kNt & BIT) != 0u) __builtin_nontemporal_store(v, gbl(p));
+    else *gbl(p) = v;
+}
+
+// ... by a value instead of a stream's bit.
+template <uint32_t NT, typename T>
+__device__ __forceinline__ T ld_as(const T* p)
+{
+    if constexpr (NT != 0u) return __builtin_nontemporal_load(gbl(p));
+    return *gbl(p);
+}
+
+template <uint32_t NT, typename T>
+__device__ __forceinline__ void st_as(T* p, T v)
+{
+    if constexpr (NT != 0u) __builtin_nontemporal_store(v, gbl(p));
     else *gbl(p) = v;
 }
 
@@ -470,17 +481,35 @@ __device__ __forceinline__ void add_stats(unsigned long long* stats, uint32_t v)
 // Why: the passes are bound by their requests to the memory side (128-byte reads,
 // 64-byte writes, about 6 TB/s of them) and by waiting; one lane per pixel with k
 // loads per record kept every line's requests pending in L1 k times.  Measured
-// against that form, per frame: k = 8 at 1920x1080 while a store fills 138 ->
-// 106 us, k = 4 71 -> 62 us, incremental 2560x1440 34.1 -> 23.6 us at frame 2000
-// and 48 -> 42 at frame 60, 3840x2160 85 -> 81 us at frame 2000 (482 MB of requests).
-// T: the ops without the plane's row (kIncremental, kPush) have few loads in
-// flight per tile and take two where that still leaves two rounds of resident
-// waves (2560x1440 at frame 2000: T = 1 27.9 us, 2 23.6, 4 23.3; 800x600, less
-// than one round: 10.3 and 11.0); the others are faster at one (3840x2160 at frame
-// 600: 100.5 us, 105.6, 107.8).
+// against that form, per frame: k = 8 at 1280x720 after 45 frames 38 -> 32.5 us, k = 16 at
+// 1920x1080 276 -> 173, incremental 2560x1440 at frame 1200, k = 4 37.5 -> 28 and k = 2
+// 31.5 -> 20, update-only 3840x2160, k = 2 53 -> 34.5.
 // ---------------------------------------------------------------------------
-constexpr bool takes_two_tiles(int op) { return op == kIncremental || op == kPush; }
-constexpr uint32_t kTwoTilesItems = 4096u;      // items from which they do: 2 x 8192 resident waves
+// T, the tiles per wave: the ops without the plane's row (kIncremental, kPush) have
+// few loads in flight per tile and take two where lists are short enough for one
+// round, that is up to 4 slots and where the records fit the Infinity Cache or, beyond,
+// once few pixels change (us, one tile / two: incremental k = 4 at 2560x1440, frame 1200
+// 31 / 28, at 3840x2160, frame 50 184 / 189, frame 1200 72.8 / 76; k = 3 at frame 100
+// 134.7 / 139, 400 91.6 / 94, 800 78 / 70; k = 1 at 7680x4320, frame 45 274 / 288, 400
+// 212 / 150; update-only k = 4 at 3840x2160, frame 50 134 / 138, 400 74.5 / 77, 1200
+// 55.8 / 51.6; k = 8 at 1920x1080 incremental 59 / 63.8 with either list), and where
+// that still leaves a whole round of resident waves (2 x 8192; 800x600, less than one:
+// 10.3 / 11.0).
+inline bool takes_two_tiles(const FrameDesc& d, int op)
+{
+    const uint64_t records = (uint64_t)d.width * d.height * d.k * 16u;
+    return d.k <= 4u && d.items >= 4096u &&
+           (records <= kCacheBytes || d.t >= (op == kPush ? 128u : 256u) * d.k);
+}
+
+// Whether the scattered stores of a changed pixel's resolve are non-temporal.
+// kCached (the plane): no; rewriting 12 bytes of a line that was just read
+// is cheaper through L2 once the records are larger than the Infinity Cache (3840x2160,
+// k = 4, frame 80: 196 us against 214).  While they fit, the cache is better left to them:
+// kCachedNt 1920x1080, k = 4 44.7 -> 41.5, k = 8 1280x720 32.5 -> 30, behind the
+// mip generator at 1920x1080, k = 4 58.5 -> 50.  kIncremental (the output) up to 4 slots: 3840x2160, k = 2
+// 95 -> 79.6, 1280x720, k = 4 while filling 30.4 -> 28; at 8 145 -> 150 (2560x1440).
+constexpr uint32_t scattered_nt(int k, int op) { return op == kCachedNt || (op == kIncremental && k >= 1 && k <= 4); }
 
 __device__ __forceinline__ void wave_lds_fence()
 {
@@ -543,16 +572,30 @@ __device__ __forceinline__ float group_sum(float v, uint32_t kk)
     return s;
 }
 
-// The list's n pixels: entry {x, y, weight, replaced slots | level << 16}.  A
-// group of lanes takes a pixel, 64 / group pixels a round.  Kept slots are read,
-// replaced slots stored (whole records, as whole_tile has them: 6% slower here, where
-// few pixels change).  The resolve goes to the list and the plane (kCached) or to
-// the output (kIncremental).  Returns the lane's replaced slots.  (Loading 2, 4 or 8
-// rounds ahead of the first: within 1% at 2, slower beyond, for the registers.)
-template <int K, int OP, bool FOV, bool TAME>
-__device__ __forceinline__ uint32_t listed_pixels(const FrameDesc& d, const FovSrc* fs, uint4* list, uint32_t n)
+template <int T>
+struct ListShare {                              // one wave's listed pixels
+    uint4 pixel[64 * T];                        // {x, y, weight, replaced slots | level << 16}
+    float4 colour[64 * T];                      // the new colour (colours_first), then the resolve (kCached)
+};
+
+// Whether the listed pixels' colours are loaded with one lane per pixel, before the
+// rounds, instead of in each round: beyond 4 slots, where a list takes many rounds,
+// a wave waits for them once (incremental k = 16 at 640x360 27.0 -> 21.8 us, update-only k = 8
+// at 1920x1080 38.5 -> 33.6, 640x360 steps at k = 8 13.0 -> 10.8); with few rounds it is
+// one access more (1279x719, k = 3, frame 2000 11.0 us, and 11.8 with this).
+template <int K>
+__device__ __forceinline__ bool colours_first(uint32_t kk)
 {
-    static_assert(OP == kPush || OP == kIncremental || OP == kCached, "the ops that need few records");
+    return K ? K > 4 : kk > 4u;
+}
+
+// The list's n pixels.  A group of lanes takes a pixel, 64 / group pixels a round.
+// Kept slots are read, replaced slots stored (whole records, as whole_tile has them:
+// 6% slower here, where few pixels change).  The resolve goes to the list and the plane
+// (kCached) or to the output (kIncremental).  Returns the lane's replaced slots.
+template <int K, int OP, int T, bool FOV, uint32_t NT, bool TAME>
+__device__ __forceinline__ uint32_t listed_pixels(const FrameDesc& d, const FovSrc* fs, ListShare<T>& sh, uint32_t n)
+{
     constexpr bool kResolves = OP != kPush;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t kk = K ? (uint32_t)K : d.k;
@@ -564,14 +607,20 @@ __device__ __forceinline__ uint32_t listed_pixels(const FrameDesc& d, const FovS
     for (uint32_t b = 0; b < n; b += per) {
         const uint32_t at = b + (lane >> lg);
         const bool own = at < n;
-        const uint4 entry = list[own ? at : b];     // past the end: an entry no result has replaced yet
+        const uint32_t e = own ? at : b;            // past the end: the round's first entry
+        const uint4 entry = sh.pixel[e];
         const uint32_t p = entry.y * d.width + entry.x;
         const size_t s = (size_t)p * kk + (slot ? j : 0u);
         const bool take = slot && ((entry.w >> j) & 1u) != 0u;
         float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
         if (kResolves && !empty && slot && !take) r = ld4<kNtRecLd>(reinterpret_cast<const float4*>(d.rec) + s);
         float c0, c1, c2;
-        if constexpr (K == 1 || K == 2) {
+        if (colours_first<K>(kk)) {
+            const float4 c = sh.colour[e];
+            c0 = c.x;
+            c1 = c.y;
+            c2 = c.z;
+        } else if constexpr (K == 1 || K == 2) {
             if constexpr (FOV) {
                 const float3 c = fov_colour(*fs, entry.x, entry.y, p, entry.w >> 16);
                 c0 = c.x;
@@ -608,31 +657,31 @@ __device__ __forceinline__ uint32_t listed_pixels(const FrameDesc& d, const FovS
             }
             if constexpr (kResolves) {
                 float* to = (OP == kCached ? d.res : d.out) + 3 * (size_t)p;
-                constexpr uint32_t bit = OP == kCached ? kNtResSt : 0u;    // scattered: never non-temporal
                 if constexpr (K == 1 || K == 2) {
                     if (j == 0u) {
-                        st<bit>(to + 0, q0);
-                        st<bit>(to + 1, q1);
-                        st<bit>(to + 2, q2);
+                        st_as<NT>(to + 0, q0);
+                        st_as<NT>(to + 1, q1);
+                        st_as<NT>(to + 2, q2);
                     }
                 } else if (j >= first && j < first + 3u) {
-                    st<bit>(to + (j - first), j == first ? q0 : j == first + 1u ? q1 : q2);
+                    st_as<NT>(to + (j - first), j == first ? q0 : j == first + 1u ? q1 : q2);
                 }
             }
-            if (OP == kCached && j == first)
-                list[at] = make_uint4(__builtin_bit_cast(uint32_t, q0), __builtin_bit_cast(uint32_t, q1),
-                                      __builtin_bit_cast(uint32_t, q2), 0u);
+            if (OP == kCached && j == first) sh.colour[at] = make_float4(q0, q1, q2, 0.f);
         }
     }
     return taken;
 }
 
-// The wave's 64 T pixels of work items item0 .. item0 + T - 1; list has room for
-// 64 T entries.  Returns the wave's (uniform) replaced slots + 2^16 x changed pixels.
-template <int K, int OP, int T, bool FOV = false>
-__device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t item0, uint32_t wave, uint4* list,
+// The wave's 64 T pixels of work items item0 .. item0 + T - 1.  Returns the wave's
+// (uniform) replaced slots + 2^16 x changed pixels.
+template <int K, int OPV, int T, bool FOV = false>
+__device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t item0, uint32_t wave, ListShare<T>& sh,
                                                  const FovSrc* fs = nullptr)
 {
+    constexpr int OP = OPV == kCachedNt ? kCached : OPV;
+    constexpr uint32_t NT = scattered_nt(K, OPV);
+    static_assert(OP == kPush || OP == kIncremental || OP == kCached, "the ops that need few records");
     const uint32_t lane = threadIdx.x & 63u;
 
     uint32_t x[T], y[T], p[T], lv[T], at[T];
@@ -647,9 +696,9 @@ __device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t it
         W[t] = ld<kNtWsumLd>(d.wsum + p[t]);
         if constexpr (OP == kCached) {
             const float* res = d.res + 3 * (size_t)p[t];
-            q0[t] = ld<kNtResLd>(res + 0);
-            q1[t] = ld<kNtResLd>(res + 1);
-            q2[t] = ld<kNtResLd>(res + 2);
+            q0[t] = ld_as<NT>(res + 0);
+            q1[t] = ld_as<NT>(res + 1);
+            q2[t] = ld_as<NT>(res + 2);
         }
     }
     uint32_t n = 0u;
@@ -663,15 +712,25 @@ __device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t it
         at[t] = 0xFFFFFFFFu;
         if (tk) {
             at[t] = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(took >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)took, 0u));
-            list[at[t]] = make_uint4(x[t], y[t], __builtin_bit_cast(uint32_t, w), tk | (lv[t] << 16));
+            sh.pixel[at[t]] = make_uint4(x[t], y[t], __builtin_bit_cast(uint32_t, w), tk | (lv[t] << 16));
+            if (colours_first<K>(d.k)) {
+                float3 c;
+                if constexpr (FOV) {
+                    c = fov_colour(*fs, x[t], y[t], p[t], lv[t]);
+                } else {
+                    const float* color = d.color + 3 * (size_t)p[t];
+                    c = make_float3(ld<kNtColor>(color + 0), ld<kNtColor>(color + 1), ld<kNtColor>(color + 2));
+                }
+                sh.colour[at[t]] = make_float4(c.x, c.y, c.z, 0.f);
+            }
         }
         n += (uint32_t)__builtin_popcountll(took);
     }
     wave_lds_fence();
     uint32_t slots = 0u;
     if (n) {
-        if (OP == kPush || d.tame) slots = listed_pixels<K, OP, FOV, true>(d, fs, list, n);
-        else slots = listed_pixels<K, OP, FOV, false>(d, fs, list, n);
+        if (OP == kPush || d.tame) slots = listed_pixels<K, OP, T, FOV, NT, true>(d, fs, sh, n);
+        else slots = listed_pixels<K, OP, T, FOV, NT, false>(d, fs, sh, n);
         slots = wave_sum(slots);
     }
     wave_lds_fence();
@@ -681,10 +740,10 @@ __device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t it
         st<kNtWsumSt>(d.wsum + p[t], W[t]);
         if constexpr (OP == kCached) {
             if (at[t] != 0xFFFFFFFFu) {
-                const uint4 v = list[at[t]];
-                q0[t] = __builtin_bit_cast(float, v.x);
-                q1[t] = __builtin_bit_cast(float, v.y);
-                q2[t] = __builtin_bit_cast(float, v.z);
+                const float4 v = sh.colour[at[t]];
+                q0[t] = v.x;
+                q1[t] = v.y;
+                q2[t] = v.z;
             }
             float* o = d.out + 3 * (size_t)p[t];
             st<kNtOut>(o + 0, q0[t]);
@@ -1181,8 +1240,8 @@ __device__ __forceinline__ void frame_block(const FrameDesc& d, uint32_t block, 
         const uint32_t n = whole_tile<K, OP, FOV>(d, block, wave, share[wave], fs);
         if (OP != kResolve && d.stats) add_stats_uniform(d.stats, n);
     } else {
-        __shared__ uint4 list[kBlock / 64][64 * T];
-        const uint32_t n = stream_tiles<K, OP, T, FOV>(d, T * block, wave, list[wave], fs);
+        __shared__ ListShare<T> share[kBlock / 64];
+        const uint32_t n = stream_tiles<K, OP, T, FOV>(d, T * block, wave, share[wave], fs);
         if (d.stats) add_stats_uniform(d.stats, n);
     }
 }
@@ -1229,12 +1288,12 @@ void frame_kernel(FrameDesc d)
 // per-slot modes (PS) also a share (per_slot_tile).
 template <bool PS>
 union TickShare {
-    uint4 list[64];
+    ListShare<1> list;
     WholeShare whole;
 };
 template <>
 union TickShare<true> {
-    uint4 list[64];
+    ListShare<1> list;
     WholeShare whole;
     PerSlotShare<0> slots;
     PerSlotShare<1> slots1;
@@ -1260,6 +1319,7 @@ __device__ __forceinline__ void tick_item(const FrameDesc& d, uint32_t local, ui
     uint32_t n = 0u;
 #define FWRS_TICK_OPS(KK)                                                        \
     n = d.op == kCached ? stream_tiles<KK, kCached, 1>(d, local, wave, sh.list)  \
+      : d.op == kCachedNt ? stream_tiles<KK, kCachedNt, 1>(d, local, wave, sh.list) \
       : d.op == kFill ? whole_tile<KK, kFill>(d, local, wave, sh.whole)          \
                       : whole_tile<KK, kFused>(d, local, wave, sh.whole)
     switch (d.k) {
@@ -1859,6 +1919,15 @@ template <int OP, int T>
 static hipError_t launch_shared(const FrameDesc& d, hipStream_t stream)
 {
     const dim3 grid((d.items + (uint32_t)T - 1u) / (uint32_t)T), block(kBlock);
+    if constexpr (T == 2) {
+        switch (d.k) {
+            case 1: hipLaunchKernelGGL((frame_kernel<1, OP, false, T>), grid, block, 0, stream, d); break;
+            case 2: hipLaunchKernelGGL((frame_kernel<2, OP, false, T>), grid, block, 0, stream, d); break;
+            case 4: hipLaunchKernelGGL((frame_kernel<4, OP, false, T>), grid, block, 0, stream, d); break;
+            default: hipLaunchKernelGGL((frame_kernel<0, OP, false, T>), grid, block, 0, stream, d); break;
+        }
+        return hipGetLastError();
+    }
     switch (d.k) {
         case 1: hipLaunchKernelGGL((frame_kernel<1, OP, false, T>), grid, block, 0, stream, d); break;
         case 2: hipLaunchKernelGGL((frame_kernel<2, OP, false, T>), grid, block, 0, stream, d); break;
@@ -1896,8 +1965,8 @@ static hipError_t launch_frame_op(const FrameDesc& d, hipStream_t stream)
             return hipGetLastError();
         }
     }
-    if constexpr (takes_two_tiles(OP)) {
-        if (d.items >= kTwoTilesItems) return launch_shared<OP, 2>(d, stream);
+    if constexpr (OP == kIncremental || OP == kPush) {
+        if (takes_two_tiles(d, OP)) return launch_shared<OP, 2>(d, stream);
     }
     return launch_shared<OP, 1>(d, stream);
 }
@@ -1910,6 +1979,7 @@ hipError_t launch_frame(const FrameDesc& d, int op, hipStream_t stream)
         case kResolve: return launch_frame_op<kResolve>(d, stream);
         case kIncremental: return launch_frame_op<kIncremental>(d, stream);
         case kCached: return launch_frame_op<kCached>(d, stream);
+        case kCachedNt: return launch_frame_op<kCachedNt>(d, stream);
         case kFill: return launch_frame_op<kFill>(d, stream);
         default: return launch_frame_op<kFused>(d, stream);
     }
@@ -2029,6 +2099,7 @@ hipError_t launch_foveated(const FovDesc& fd, int op, hipStream_t stream)
 #define FWRS_FOV_OPS(KK)                                      \
     do {                                                      \
         if (op == kCached) FWRS_FOV_LAUNCH(KK, false, kCached);   \
+        else if (op == kCachedNt) FWRS_FOV_LAUNCH(KK, false, kCachedNt); \
         else if (op == kFill) FWRS_FOV_LAUNCH(KK, false, kFill);  \
         else if (op == kPush) FWRS_FOV_LAUNCH(KK, false, kPush);  \
         else FWRS_FOV_LAUNCH(KK, false, kFused);              \
