@@ -933,6 +933,39 @@ __device__ __forceinline__ bool decide_eq7(const FrameDesc& d, uint32_t word, fl
     return decide_eq7_as<false>(word, W, w, dl, s);
 }
 
+// rgb_to_lab of a colour that all lanes of a quad hold, one curve per lane.  The whole
+// quad is active.
+__device__ __forceinline__ float3 rgb_to_lab_quad(float r, float g, float b)
+{
+    const uint32_t q = threadIdx.x & 3u;
+    const float m0 = q == 0u ? 0.4124564f : q == 1u ? 0.2126729f : 0.0193339f;
+    const float m1 = q == 0u ? 0.3575761f : q == 1u ? 0.7151522f : 0.1191920f;
+    const float m2 = q == 0u ? 0.1804375f : q == 1u ? 0.0721750f : 0.9503041f;
+    const float c = q == 0u ? 0.95047f : q == 1u ? 1.0f : 1.08883f;
+    const float rc = q == 0u ? 0x1.0d5728p+0f : q == 1u ? 1.0f : 0x1.d63ac2p-1f;
+    const float f = lab_curve(div_const((m0 * r + m1 * g) + m2 * b, c, rc));     // x / 1 is x
+    const float fx = quad_perm<0, 0, 0, 0>(f), fy = quad_perm<1, 1, 1, 1>(f), fz = quad_perm<2, 2, 2, 2>(f);
+    return make_float3(116.0f * fy - 16.0f, 500.0f * (fx - fy), 200.0f * (fy - fz));
+}
+
+// Eq. 7's |dL| of a slot's sample against its pixel's new colour, every lane of the wave
+// active.  A sample with the new colour has |dL| = 0 exactly (same_colour): Lab and
+// CIE94 are evaluated only where some slot of the wave differs, the new colour's Lab
+// once per quad from 3 slots on.
+template <int K>
+__device__ __forceinline__ float slot_delta(const float4& s, const float4& c)
+{
+    const bool differs = !(lab_bounded(c.x, c.y, c.z) && same_colour(s, c.x, c.y, c.z));
+    float dl = 0.0f;
+    if (__ballot(differs) != 0u) {
+        float3 lab;
+        if constexpr (K == 1 || K == 2) lab = rgb_to_lab(c.x, c.y, c.z);
+        else lab = rgb_to_lab_quad(c.x, c.y, c.z);
+        if (differs) dl = delta_l(s.y, s.z, s.w, lab);
+    }
+    return dl;
+}
+
 // ---------------------------------------------------------------------------
 // A frame of a per-slot mode, one value per slot in wsum[p * k + j]:
 //  - Eq. 7 (FULL): the slot's own w_sum, biased by the slot's colour
@@ -948,25 +981,12 @@ __device__ __forceinline__ bool decide_eq7(const FrameDesc& d, uint32_t word, fl
 // LDS to leave by rows.  Against one lane per pixel streaming its record slot by
 // slot, as ticks and slot counts other than 4 and 8 had it: four 900x600 Eq. 7
 // sessions in a tick 82.4 -> 44.5 us, five 700x500 A-ES k = 8 sessions 170 -> 54,
-// 1600x1000 Eq. 7 k = 3 49 -> 39, k = 1 21.2 -> 15.4.
+// 1600x1000 Eq. 7 k = 1 21.2 -> 15.4, 1920x1080 k = 16 1283 -> 248.
+// Non-temporal record loads gain 10% where other sessions' frames come in between (three
+// 2560x1440 sessions, Eq. 7, k = 4: 89 us against 99) and lose 20 to 40% where one session
+// runs frame after frame, whose next frame finds part of its store in the Infinity
+// Cache (109 us against 87), so they are plain.
 // ---------------------------------------------------------------------------
-// Whether a frame's store is larger than the 256 MB Infinity Cache (20 bytes per
-// slot and a value): its records are then read non-temporally, which leaves the
-// cache to the partial lines that replaced slots write (2560x1440 Eq. 7, k = 4,
-// three sessions in turn: 99.8 -> 89.9 us; a store that fits: 800x600 16.4 ->
-// 17.7), and at k = 4 and 8 smaller stores take one lane per pixel (800x600 14.8
-// us against 16.4; 1600x1000 A-ES k = 4 31 either way).
-inline bool store_streams(const FrameDesc& d)
-{
-    return (uint64_t)d.width * d.height * d.k * 24u > (256ull << 20);
-}
-
-__device__ __forceinline__ float4 ld4_streamed(const float4* p)
-{
-    const v4f v = __builtin_nontemporal_load(gbl(reinterpret_cast<const v4f*>(p)));
-    return make_float4(v.x, v.y, v.z, v.w);
-}
-
 template <int K>
 struct PerSlotShare {                           // one wave's pixels
     static constexpr int kBlocks = K ? (K + 3) / 4 : (kMaxK + 3) / 4;
@@ -975,7 +995,7 @@ struct PerSlotShare {                           // one wave's pixels
     uint32_t words[64][4 * kBlocks];            // Philox words, one per slot
 };
 
-template <int K, int OP, bool FOV = false, bool STREAMED = false>
+template <int K, int OP, bool FOV = false>
 __device__ __forceinline__ uint32_t per_slot_tile(const FrameDesc& d, uint32_t item, uint32_t wave,
                                                   PerSlotShare<K>& sh, const FovSrc* fs = nullptr)
 {
@@ -1018,9 +1038,7 @@ __device__ __forceinline__ uint32_t per_slot_tile(const FrameDesc& d, uint32_t i
     auto load = [&](uint32_t b, float4& rec, float& val) {
         const uint32_t q = sh.pixel[b + (lane >> lg)].x;
         const size_t at = (size_t)q * kk + (slot ? j : 0u);
-        const float4* from = reinterpret_cast<const float4*>(d.rec) + at;
-        if constexpr (STREAMED) rec = ld4_streamed(from);
-        else rec = ld4<kNtRecLd>(from);
+        rec = ld4<kNtRecLd>(reinterpret_cast<const float4*>(d.rec) + at);
         val = ld<kNtWsumLd>(d.wsum + at);
     };
 #pragma unroll
@@ -1058,13 +1076,8 @@ __device__ __forceinline__ uint32_t per_slot_tile(const FrameDesc& d, uint32_t i
             take = kn > Wj;
             s = take ? kn : Wj;
         } else {
-            // Eq. 7 against this slot's sample, then the slot's Alg. 2 decision.  A
-            // sample with the new pixel's colour has |dL| = 0 exactly (same_colour):
-            // its Lab and CIE94 are not evaluated.
-            float dl = 0.0f;
-            if (!(lab_bounded(c.x, c.y, c.z) && same_colour(r, c.x, c.y, c.z)))
-                dl = delta_l(r.y, r.z, r.w, rgb_to_lab(c.x, c.y, c.z));
-            take = decide_eq7(d, word, Wj, w, dl, s);
+            // Eq. 7 against this slot's sample, then the slot's Alg. 2 decision
+            take = decide_eq7(d, word, Wj, w, slot_delta<K>(r, c), s);
         }
         const bool own = slot && now.y != 0u;
         take = take && own;
@@ -1104,14 +1117,16 @@ __device__ __forceinline__ uint32_t per_slot_tile(const FrameDesc& d, uint32_t i
 }
 
 // The same with one lane per pixel, the record and values in registers: fewer
-// instructions per pixel, which counts where the store stays in the Infinity
-// Cache (store_streams).
+// instructions per pixel, which counts where colours differ everywhere (k = 3 and 4 at
+// 3840x2160 with every colour changing: 210 and 267 us, one lane per slot 307 and 297;
+// k = 8 at 1920x1080 137 and 148).  For the slot counts it is compiled for, but not 1 and
+// 2, where one lane per slot is as short and reads whole lines (k = 2 at 1920x1080 32 us
+// against 43).
 template <int K, int OP, bool FOV = false>
 __device__ __forceinline__ uint32_t pixel_per_slot(const FrameDesc& d, uint32_t x, uint32_t y,
                                                    const FovSrc* fs = nullptr)
 {
     const uint32_t p = y * d.width + x;
-    static_assert(K > 0 && K % 4 == 0, "whole Philox blocks, 16-byte groups of values");
     constexpr bool kUpdates = OP == kPush || OP == kFused || OP == kIncremental;
     constexpr bool kResolves = OP == kFused || OP == kIncremental;
     float4* rec = reinterpret_cast<float4*>(d.rec) + (size_t)p * K;
@@ -1123,13 +1138,18 @@ __device__ __forceinline__ uint32_t pixel_per_slot(const FrameDesc& d, uint32_t 
     float W[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) r[j] = ld4<kNtRecLd>(rec + j);
+    if constexpr (K % 4 == 0) {
 #pragma unroll
-    for (int j = 0; j < K; j += 4) {
-        const float4 v = ld4<kNtWsumLd>(reinterpret_cast<const float4*>(wslot + j));
-        W[j] = v.x;
-        W[j + 1] = v.y;
-        W[j + 2] = v.z;
-        W[j + 3] = v.w;
+        for (int j = 0; j < K; j += 4) {
+            const float4 v = ld4<kNtWsumLd>(reinterpret_cast<const float4*>(wslot + j));
+            W[j] = v.x;
+            W[j + 1] = v.y;
+            W[j + 2] = v.z;
+            W[j + 3] = v.w;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < K; ++j) W[j] = ld<kNtWsumLd>(wslot + j);
     }
     uint32_t lv;
     float c0, c1, c2;
@@ -1196,9 +1216,14 @@ __device__ __forceinline__ uint32_t pixel_per_slot(const FrameDesc& d, uint32_t 
         a1 = a1 + v.x * v.z;
         a2 = a2 + v.x * v.w;
     }
+    if constexpr (K % 4 == 0) {
 #pragma unroll
-    for (int j = 0; j < K; j += 4)
-        st4<kNtWsumSt>(reinterpret_cast<float4*>(wslot + j), make_float4(W[j], W[j + 1], W[j + 2], W[j + 3]));
+        for (int j = 0; j < K; j += 4)
+            st4<kNtWsumSt>(reinterpret_cast<float4*>(wslot + j), make_float4(W[j], W[j + 1], W[j + 2], W[j + 3]));
+    } else {
+#pragma unroll
+        for (int j = 0; j < K; ++j) st<kNtWsumSt>(wslot + j, W[j]);
+    }
     if (kResolves && (OP != kIncremental || tk)) {
         const float rs = resolve_scale(d, S);
         float* o = d.out + 3 * (size_t)p;
@@ -1220,7 +1245,7 @@ __device__ __forceinline__ uint32_t frame_item(uint32_t block, uint32_t items, u
 }
 
 // Work items [T block, T block + T) of a frame.  Per-slot modes, an item per block:
-// T = 0 one lane per pixel, 1 one lane per slot, 2 the same with streamed records.
+// T = 0 one lane per pixel, 1 one lane per slot.
 template <int K, int OP, bool PER_SLOT, int T, bool FOV>
 __device__ __forceinline__ void frame_block(const FrameDesc& d, uint32_t block, const FovSrc* fs)
 {
@@ -1231,7 +1256,7 @@ __device__ __forceinline__ void frame_block(const FrameDesc& d, uint32_t block, 
         if (d.stats) add_stats(d.stats, n);
     } else if constexpr (PER_SLOT) {
         __shared__ PerSlotShare<K> share[kBlock / 64];
-        const uint32_t n = per_slot_tile<K, OP, FOV, T == 2>(d, block, wave, share[wave], fs);
+        const uint32_t n = per_slot_tile<K, OP, FOV>(d, block, wave, share[wave], fs);
         if (d.stats) add_stats_uniform(d.stats, n);
     } else if constexpr (OP == kResolve && K > 0) {
         resolve_pixel<K>(d, block, wave);
@@ -1246,18 +1271,22 @@ __device__ __forceinline__ void frame_block(const FrameDesc& d, uint32_t block, 
     }
 }
 
-// Waves per SIMD the frame kernels are compiled for (T = 0: no bound).
-constexpr int kFrameWaves = 8;
-
-// ... and the most they run with: resolve_pixel reads a record in k accesses, which
-// eight waves a SIMD push out of L1 between the first and the last (3840x2160, k = 8:
-// 213 us with 8 waves, 191 with 6, 188 with 4, 216 with 2; k = 4 107, 106, 103 and
-// 110; k = 2 49.5, 50.7, 52.5 and 69).
-constexpr int frame_waves(int k, int op, int t) { return op == kResolve && k >= 4 ? 4 : t ? kFrameWaves : 1; }
-constexpr int frame_waves_most(int k, int op) { return op == kResolve && k >= 4 ? 4 : 8; }
+// Waves per SIMD the frame kernels are compiled for and the most they run with.
+// One lane per pixel reads a record in k accesses, which eight waves a SIMD push out
+// of L1 between the first and the last.  resolve_pixel at 3840x2160: k = 8 213 us with 8
+// waves, 191 with 6, 188 with 4, 216 with 2; k = 4 107, 106, 103 and 110; k = 2 49.5, 50.7,
+// 52.5 and 69.  pixel_per_slot (T = 0), Eq. 7 and k = 4 at 3840x2160: 238.5 us with 8, 233.8
+// with 5, 229 with 3; with every colour changing 263, 268 and 294.
+struct Waves {
+    int least, most;
+};
+constexpr Waves frame_waves(int k, int op, int t)
+{
+    return op == kResolve && k >= 4 ? Waves{4, 4} : t == 0 ? Waves{5, 5} : Waves{8, 8};
+}
 
 template <int K, int OP, bool PER_SLOT = false, int T = 1>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(frame_waves(K, OP, T), frame_waves_most(K, OP))))
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(frame_waves(K, OP, T).least, frame_waves(K, OP, T).most)))
 void frame_kernel(FrameDesc d)
 {
     frame_block<K, OP, PER_SLOT, T, false>(d, frame_item(blockIdx.x, gridDim.x, d.t), nullptr);
@@ -1552,11 +1581,7 @@ __device__ __forceinline__ void reproject_tile(const ReprojDesc& r, uint32_t ite
                 take = kn > Wj;
                 sj = take ? kn : Wj;
             } else {
-                // Eq. 7: a sample with the new pixel's colour has |dL| = 0 exactly (same_colour)
-                float dl = 0.0f;
-                if (!(lab_bounded(c.x, c.y, c.z) && same_colour(t, c.x, c.y, c.z)))
-                    dl = delta_l(t.y, t.z, t.w, rgb_to_lab(c.x, c.y, c.z));
-                take = decide_eq7(d, word, Wj, c.w, dl, sj);
+                take = decide_eq7(d, word, Wj, c.w, slot_delta<K>(t, c), sj);
             }
         }
         const bool own = slot && (px.z & 1u) != 0u;
@@ -1901,7 +1926,8 @@ __global__ __launch_bounds__(kBlock) void foveate_kernel(FoveateArgs a)
 }
 
 template <int K, bool PER_SLOT, int OP, int T = 1>
-__global__ __launch_bounds__(kBlock, T ? kFrameWaves : 1) void foveated_kernel(FovDesc fd)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(frame_waves(K, OP, T).least, frame_waves(K, OP, T).most)))
+void foveated_kernel(FovDesc fd)
 {
     frame_block<K, OP, PER_SLOT, T, true>(fd.f, frame_item(blockIdx.x, gridDim.x, fd.f.t), &fd.s);
 }
@@ -1938,19 +1964,6 @@ static hipError_t launch_shared(const FrameDesc& d, hipStream_t stream)
     return hipGetLastError();
 }
 
-template <int OP, int T>
-static void launch_per_slot(const FrameDesc& d, hipStream_t stream)
-{
-    const dim3 grid(d.items), block(kBlock);
-    switch (d.k) {
-        case 1: hipLaunchKernelGGL((frame_kernel<1, OP, true, T>), grid, block, 0, stream, d); break;
-        case 2: hipLaunchKernelGGL((frame_kernel<2, OP, true, T>), grid, block, 0, stream, d); break;
-        case 4: hipLaunchKernelGGL((frame_kernel<4, OP, true, T>), grid, block, 0, stream, d); break;
-        case 8: hipLaunchKernelGGL((frame_kernel<8, OP, true, T>), grid, block, 0, stream, d); break;
-        default: hipLaunchKernelGGL((frame_kernel<0, OP, true, T>), grid, block, 0, stream, d); break;
-    }
-}
-
 template <int OP>
 static hipError_t launch_frame_op(const FrameDesc& d, hipStream_t stream)
 {
@@ -1958,10 +1971,15 @@ static hipError_t launch_frame_op(const FrameDesc& d, hipStream_t stream)
     if constexpr (OP == kPush || OP == kFused || OP == kIncremental) {
         if (per_slot_mode(d.bias)) {
             const dim3 grid(d.items), block(kBlock);
-            if (store_streams(d)) launch_per_slot<OP, 2>(d, stream);
-            else if (d.k == 4u) hipLaunchKernelGGL((frame_kernel<4, OP, true, 0>), grid, block, 0, stream, d);
-            else if (d.k == 8u) hipLaunchKernelGGL((frame_kernel<8, OP, true, 0>), grid, block, 0, stream, d);
-            else launch_per_slot<OP, 1>(d, stream);
+            switch (d.k) {
+                case 1: hipLaunchKernelGGL((frame_kernel<1, OP, true, 1>), grid, block, 0, stream, d); break;
+                case 2: hipLaunchKernelGGL((frame_kernel<2, OP, true, 1>), grid, block, 0, stream, d); break;
+                case 3: hipLaunchKernelGGL((frame_kernel<3, OP, true, 0>), grid, block, 0, stream, d); break;
+                case 4: hipLaunchKernelGGL((frame_kernel<4, OP, true, 0>), grid, block, 0, stream, d); break;
+                case 5: hipLaunchKernelGGL((frame_kernel<5, OP, true, 0>), grid, block, 0, stream, d); break;
+                case 8: hipLaunchKernelGGL((frame_kernel<8, OP, true, 0>), grid, block, 0, stream, d); break;
+                default: hipLaunchKernelGGL((frame_kernel<0, OP, true, 1>), grid, block, 0, stream, d); break;
+            }
             return hipGetLastError();
         }
     }
@@ -2105,25 +2123,20 @@ hipError_t launch_foveated(const FovDesc& fd, int op, hipStream_t stream)
         else FWRS_FOV_LAUNCH(KK, false, kFused);              \
     } while (0)
     if (ps) {
-        const bool push = op == kPush;
-        if (fd.f.k == 1) {
-            if (push) FWRS_FOV_LAUNCH(1, true, kPush);
-            else FWRS_FOV_LAUNCH(1, true, kFused);
-        } else if (fd.f.k == 2) {
-            if (push) FWRS_FOV_LAUNCH(2, true, kPush);
-            else FWRS_FOV_LAUNCH(2, true, kFused);
-        } else if (fd.f.k == 4) {
-            if (store_streams(fd.f)) {
-                if (push) hipLaunchKernelGGL((foveated_kernel<4, true, kPush, 2>), grid, block, 0, stream, fd);
-                else hipLaunchKernelGGL((foveated_kernel<4, true, kFused, 2>), grid, block, 0, stream, fd);
-            } else {
-                if (push) hipLaunchKernelGGL((foveated_kernel<4, true, kPush, 0>), grid, block, 0, stream, fd);
-                else hipLaunchKernelGGL((foveated_kernel<4, true, kFused, 0>), grid, block, 0, stream, fd);
-            }
-        } else {
-            if (push) FWRS_FOV_LAUNCH(0, true, kPush);
-            else FWRS_FOV_LAUNCH(0, true, kFused);
+#define FWRS_FOV_PER_SLOT(KK, T)                                                                                 \
+    do {                                                                                                         \
+        if (op == kPush) hipLaunchKernelGGL((foveated_kernel<KK, true, kPush, T>), grid, block, 0, stream, fd);  \
+        else hipLaunchKernelGGL((foveated_kernel<KK, true, kFused, T>), grid, block, 0, stream, fd);             \
+    } while (0)
+        switch (fd.f.k) {
+            case 1: FWRS_FOV_PER_SLOT(1, 1); break;
+            case 2: FWRS_FOV_PER_SLOT(2, 1); break;
+            case 3: FWRS_FOV_PER_SLOT(3, 0); break;
+            case 4: FWRS_FOV_PER_SLOT(4, 0); break;
+            case 5: FWRS_FOV_PER_SLOT(5, 0); break;
+            default: FWRS_FOV_PER_SLOT(0, 1); break;
         }
+#undef FWRS_FOV_PER_SLOT
     } else {
         switch (fd.f.k) {
             case 4: FWRS_FOV_OPS(4); break;
