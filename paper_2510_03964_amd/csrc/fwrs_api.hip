@@ -825,8 +825,10 @@ int layout_tick(const fwrs_frame* frames, int n, bool reverse, TileFn tile, Tick
         const int op = nf > 1 && group_kernel(x) ? fwrs::kOpGroup : fused_op_at(x, d.t, plane, records);
         w.plane[g] = (plane_after(x, op) ? 1 : 0) | (tame ? 2 : 0);
         d.tame = tame ? 1u : 0u;
-        if (nf > 1 && groups_kind != fwrs::kTickGroups8)
-            groups_kind = op == fwrs::kOpGroup && x->k == 8 ? fwrs::kTickGroups8 : fwrs::kTickGroups;
+        if (nf > 1)
+            groups_kind = std::max(groups_kind, op != fwrs::kOpGroup ? fwrs::kTickStored
+                                                : x->k == 8          ? fwrs::kTickGroups8
+                                                                     : fwrs::kTickGroups);
         per_slot = per_slot || fwrs::per_slot_mode(x->prm.bias_mode);
         ops[i] = op;
         d.op = (uint32_t)op;

@@ -44,13 +44,15 @@ inline size_t tick_table_bytes(size_t frames) { return kTickDescOffset + frames 
 // The batched kernel on `grid` blocks, one per work item of the table's tick
 // (grid = head.total; blocks past the last item do nothing), in the
 // instantiation for the kind of tick the table holds: no groups (no leader
-// with nf > 1), groups, or groups among which one with op kOpGroup and k = 8;
-// plus kTickPerSlot if some frame's mode keeps one value per slot.
+// with nf > 1), groups that all go through the store frame by frame, groups among
+// which some with op kOpGroup, or some of these with k = 8; plus kTickPerSlot if
+// some frame's mode keeps one value per slot.
 constexpr int kTickAlone = 0;
-constexpr int kTickGroups = 1;
-constexpr int kTickGroups8 = 2;
-constexpr int kTickPerSlot = 3;
-constexpr int kTickKinds = 6;
+constexpr int kTickStored = 1;
+constexpr int kTickGroups = 2;
+constexpr int kTickGroups8 = 3;
+constexpr int kTickPerSlot = 4;
+constexpr int kTickKinds = 8;
 hipError_t launch_tick(const void* table, uint32_t grid, int kind, hipStream_t stream);
 // Its entry points, for HIP graph kernel nodes: arguments (const TickHead*, const FrameDesc*).
 void* tick_kernel_entry(int kind);

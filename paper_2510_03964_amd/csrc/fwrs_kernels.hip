@@ -594,10 +594,10 @@ __device__ __forceinline__ bool colours_first(uint32_t kk)
 // 6% slower here, where few pixels change).  The resolve goes to the list and the plane
 // (kCached) or to the output (kIncremental).  Returns the lane's replaced slots.
 template <int K, int OP, int T, bool FOV, uint32_t NT, bool TAME>
-__device__ __forceinline__ uint32_t listed_pixels(const FrameDesc& d, const FovSrc* fs, ListShare<T>& sh, uint32_t n)
+__device__ __forceinline__ uint32_t listed_pixels(const FrameDesc& d, const FovSrc* fs, ListShare<T>& sh, uint32_t n,
+                                                  uint32_t lane)
 {
     constexpr bool kResolves = OP != kPush;
-    const uint32_t lane = threadIdx.x & 63u;
     const uint32_t kk = K ? (uint32_t)K : d.k;
     const uint32_t lg = group_log2<K>(kk), first = group_first<K>(kk);
     const uint32_t j = lane & ((1u << lg) - 1u), per = 64u >> lg;
@@ -676,13 +676,12 @@ __device__ __forceinline__ uint32_t listed_pixels(const FrameDesc& d, const FovS
 // The wave's 64 T pixels of work items item0 .. item0 + T - 1.  Returns the wave's
 // (uniform) replaced slots + 2^16 x changed pixels.
 template <int K, int OPV, int T, bool FOV = false>
-__device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t item0, uint32_t wave, ListShare<T>& sh,
-                                                 const FovSrc* fs = nullptr)
+__device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t item0, uint32_t wave, uint32_t lane,
+                                                 ListShare<T>& sh, const FovSrc* fs = nullptr)
 {
     constexpr int OP = OPV == kCachedNt ? kCached : OPV;
     constexpr uint32_t NT = scattered_nt(K, OPV);
     static_assert(OP == kPush || OP == kIncremental || OP == kCached, "the ops that need few records");
-    const uint32_t lane = threadIdx.x & 63u;
 
     uint32_t x[T], y[T], p[T], lv[T], at[T];
     bool in[T];
@@ -729,8 +728,8 @@ __device__ __forceinline__ uint32_t stream_tiles(const FrameDesc& d, uint32_t it
     wave_lds_fence();
     uint32_t slots = 0u;
     if (n) {
-        if (OP == kPush || d.tame) slots = listed_pixels<K, OP, T, FOV, NT, true>(d, fs, sh, n);
-        else slots = listed_pixels<K, OP, T, FOV, NT, false>(d, fs, sh, n);
+        if (OP == kPush || d.tame) slots = listed_pixels<K, OP, T, FOV, NT, true>(d, fs, sh, n, lane);
+        else slots = listed_pixels<K, OP, T, FOV, NT, false>(d, fs, sh, n, lane);
         slots = wave_sum(slots);
     }
     wave_lds_fence();
@@ -797,13 +796,12 @@ struct WholeShare {                             // one wave's pixels
 };
 
 template <int K, int OP, bool FOV = false>
-__device__ __forceinline__ uint32_t whole_tile(const FrameDesc& d, uint32_t item, uint32_t wave, WholeShare& sh,
+__device__ __forceinline__ uint32_t whole_tile(const FrameDesc& d, uint32_t item, uint32_t wave, uint32_t lane, WholeShare& sh,
                                                const FovSrc* fs = nullptr)
 {
     static_assert(OP == kFused || OP == kFill || OP == kResolve, "the ops that read every record");
     constexpr bool kUpdates = OP != kResolve;
     constexpr uint32_t D = K == 0 || K == 2 || K == 4 ? 2u : 1u;    // rounds loaded ahead
-    const uint32_t lane = threadIdx.x & 63u;
     const uint32_t kk = K ? (uint32_t)K : d.k;
     const uint32_t lg = group_log2<K>(kk), first = group_first<K>(kk);
     const uint32_t j = lane & ((1u << lg) - 1u), per = 64u >> lg;
@@ -935,9 +933,9 @@ __device__ __forceinline__ bool decide_eq7(const FrameDesc& d, uint32_t word, fl
 
 // rgb_to_lab of a colour that all lanes of a quad hold, one curve per lane.  The whole
 // quad is active.
-__device__ __forceinline__ float3 rgb_to_lab_quad(float r, float g, float b)
+__device__ __forceinline__ float3 rgb_to_lab_quad(float r, float g, float b, uint32_t lane)
 {
-    const uint32_t q = threadIdx.x & 3u;
+    const uint32_t q = lane & 3u;
     const float m0 = q == 0u ? 0.4124564f : q == 1u ? 0.2126729f : 0.0193339f;
     const float m1 = q == 0u ? 0.3575761f : q == 1u ? 0.7151522f : 0.1191920f;
     const float m2 = q == 0u ? 0.1804375f : q == 1u ? 0.0721750f : 0.9503041f;
@@ -953,14 +951,14 @@ __device__ __forceinline__ float3 rgb_to_lab_quad(float r, float g, float b)
 // CIE94 are evaluated only where some slot of the wave differs, the new colour's Lab
 // once per quad from 3 slots on.
 template <int K>
-__device__ __forceinline__ float slot_delta(const float4& s, const float4& c)
+__device__ __forceinline__ float slot_delta(const float4& s, const float4& c, uint32_t lane)
 {
     const bool differs = !(lab_bounded(c.x, c.y, c.z) && same_colour(s, c.x, c.y, c.z));
     float dl = 0.0f;
     if (__ballot(differs) != 0u) {
         float3 lab;
         if constexpr (K == 1 || K == 2) lab = rgb_to_lab(c.x, c.y, c.z);
-        else lab = rgb_to_lab_quad(c.x, c.y, c.z);
+        else lab = rgb_to_lab_quad(c.x, c.y, c.z, lane);
         if (differs) dl = delta_l(s.y, s.z, s.w, lab);
     }
     return dl;
@@ -996,12 +994,11 @@ struct PerSlotShare {                           // one wave's pixels
 };
 
 template <int K, int OP, bool FOV = false>
-__device__ __forceinline__ uint32_t per_slot_tile(const FrameDesc& d, uint32_t item, uint32_t wave,
+__device__ __forceinline__ uint32_t per_slot_tile(const FrameDesc& d, uint32_t item, uint32_t wave, uint32_t lane,
                                                   PerSlotShare<K>& sh, const FovSrc* fs = nullptr)
 {
     static_assert(OP == kPush || OP == kFused || OP == kIncremental, "the resolve-only pass is the same under every mode");
     constexpr bool kResolves = OP != kPush;
-    const uint32_t lane = threadIdx.x & 63u;
     const uint32_t kk = K ? (uint32_t)K : d.k;
     const uint32_t lg = group_log2<K>(kk), first = group_first<K>(kk);
     const uint32_t j = lane & ((1u << lg) - 1u), per = 64u >> lg;
@@ -1077,7 +1074,7 @@ __device__ __forceinline__ uint32_t per_slot_tile(const FrameDesc& d, uint32_t i
             s = take ? kn : Wj;
         } else {
             // Eq. 7 against this slot's sample, then the slot's Alg. 2 decision
-            take = decide_eq7(d, word, Wj, w, slot_delta<K>(r, c), s);
+            take = decide_eq7(d, word, Wj, w, slot_delta<K>(r, c, lane), s);
         }
         const bool own = slot && now.y != 0u;
         take = take && own;
@@ -1249,24 +1246,24 @@ __device__ __forceinline__ uint32_t frame_item(uint32_t block, uint32_t items, u
 template <int K, int OP, bool PER_SLOT, int T, bool FOV>
 __device__ __forceinline__ void frame_block(const FrameDesc& d, uint32_t block, const FovSrc* fs)
 {
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
     if constexpr (PER_SLOT && T == 0) {
         uint32_t x, y, n = 0u;
-        if (item_pixel_of(d, block, wave, threadIdx.x & 63u, x, y)) n = pixel_per_slot<K, OP, FOV>(d, x, y, fs);
+        if (item_pixel_of(d, block, wave, lane, x, y)) n = pixel_per_slot<K, OP, FOV>(d, x, y, fs);
         if (d.stats) add_stats(d.stats, n);
     } else if constexpr (PER_SLOT) {
         __shared__ PerSlotShare<K> share[kBlock / 64];
-        const uint32_t n = per_slot_tile<K, OP, FOV>(d, block, wave, share[wave], fs);
+        const uint32_t n = per_slot_tile<K, OP, FOV>(d, block, wave, lane, share[wave], fs);
         if (d.stats) add_stats_uniform(d.stats, n);
     } else if constexpr (OP == kResolve && K > 0) {
         resolve_pixel<K>(d, block, wave);
     } else if constexpr (OP == kFused || OP == kFill || OP == kResolve) {
         __shared__ WholeShare share[kBlock / 64];
-        const uint32_t n = whole_tile<K, OP, FOV>(d, block, wave, share[wave], fs);
+        const uint32_t n = whole_tile<K, OP, FOV>(d, block, wave, lane, share[wave], fs);
         if (OP != kResolve && d.stats) add_stats_uniform(d.stats, n);
     } else {
         __shared__ ListShare<T> share[kBlock / 64];
-        const uint32_t n = stream_tiles<K, OP, T, FOV>(d, T * block, wave, share[wave], fs);
+        const uint32_t n = stream_tiles<K, OP, T, FOV>(d, T * block, wave, lane, share[wave], fs);
         if (d.stats) add_stats_uniform(d.stats, n);
     }
 }
@@ -1333,24 +1330,24 @@ union TickShare<true> {
 // One wave's share of a lone frame's work item; counts its replaced slots and
 // changed pixels.
 template <bool PS>
-__device__ __forceinline__ void tick_item(const FrameDesc& d, uint32_t local, uint32_t wave, TickShare<PS>& sh)
+__device__ __forceinline__ void tick_item(const FrameDesc& d, uint32_t local, uint32_t wave, uint32_t lane, TickShare<PS>& sh)
 {
     if constexpr (PS) {
         if (per_slot_mode(d.bias)) {
-            const uint32_t n = d.k == 1u   ? per_slot_tile<1, kFused>(d, local, wave, sh.slots1)
-                               : d.k == 2u ? per_slot_tile<2, kFused>(d, local, wave, sh.slots2)
-                               : d.k == 4u ? per_slot_tile<4, kFused>(d, local, wave, sh.slots4)
-                                           : per_slot_tile<0, kFused>(d, local, wave, sh.slots);
+            const uint32_t n = d.k == 1u   ? per_slot_tile<1, kFused>(d, local, wave, lane, sh.slots1)
+                               : d.k == 2u ? per_slot_tile<2, kFused>(d, local, wave, lane, sh.slots2)
+                               : d.k == 4u ? per_slot_tile<4, kFused>(d, local, wave, lane, sh.slots4)
+                                           : per_slot_tile<0, kFused>(d, local, wave, lane, sh.slots);
             if (d.stats) add_stats_uniform(d.stats, n);
             return;
         }
     }
     uint32_t n = 0u;
 #define FWRS_TICK_OPS(KK)                                                        \
-    n = d.op == kCached ? stream_tiles<KK, kCached, 1>(d, local, wave, sh.list)  \
-      : d.op == kCachedNt ? stream_tiles<KK, kCachedNt, 1>(d, local, wave, sh.list) \
-      : d.op == kFill ? whole_tile<KK, kFill>(d, local, wave, sh.whole)          \
-                      : whole_tile<KK, kFused>(d, local, wave, sh.whole)
+    n = d.op == kCached ? stream_tiles<KK, kCached, 1>(d, local, wave, lane, sh.list)  \
+      : d.op == kCachedNt ? stream_tiles<KK, kCachedNt, 1>(d, local, wave, lane, sh.list) \
+      : d.op == kFill ? whole_tile<KK, kFill>(d, local, wave, lane, sh.whole)          \
+                      : whole_tile<KK, kFused>(d, local, wave, lane, sh.whole)
     switch (d.k) {
         case 1: FWRS_TICK_OPS(1); break;
         case 2: FWRS_TICK_OPS(2); break;
@@ -1362,46 +1359,34 @@ __device__ __forceinline__ void tick_item(const FrameDesc& d, uint32_t local, ui
     if (d.stats) add_stats_uniform(d.stats, n);
 }
 
-// One work item of a group of d.nf > 1 frames (d its leader); G, PS as tick_blocks'.
-template <int G, bool PS>
+// One work item of a group run by pixel_group (d its leader); G as tick_blocks'.
+template <int G>
 __device__ __forceinline__ void tick_group_item(const FrameDesc& d, const FrameDesc* __restrict__ descs,
-                                                uint32_t local, uint32_t wave, TickShare<PS>& sh)
+                                                uint32_t local, uint32_t wave)
 {
     const FrameDesc* later = descs + d.more;
-    if (d.op == kGroup) {
-        uint32_t x, y, slots = 0u, changed = 0u;
-        if (item_pixel_of(d, local, wave, threadIdx.x & 63u, x, y)) {
-            switch (d.k) {
-                case 1: pixel_group<1>(d, later, x, y, slots, changed); break;
-                case 2: pixel_group<2>(d, later, x, y, slots, changed); break;
-                case 4: pixel_group<4>(d, later, x, y, slots, changed); break;
-                default:                                 // the host sets kGroup only for k in {1, 2, 4, 8}
-                    if constexpr (G == kTickGroups8) pixel_group<8>(d, later, x, y, slots, changed);
-                    break;
-            }
+    uint32_t x, y, slots = 0u, changed = 0u;
+    if (item_pixel_of(d, local, wave, threadIdx.x & 63u, x, y)) {
+        switch (d.k) {
+            case 1: pixel_group<1>(d, later, x, y, slots, changed); break;
+            case 2: pixel_group<2>(d, later, x, y, slots, changed); break;
+            case 4: pixel_group<4>(d, later, x, y, slots, changed); break;
+            default:                                     // the host sets kGroup only for k in {1, 2, 4, 8}
+                if constexpr (G == kTickGroups8) pixel_group<8>(d, later, x, y, slots, changed);
+                break;
         }
-        if (d.stats) add_stats_wide(d.stats, slots, changed);
-        return;
     }
-    for (uint32_t f = 0; f < d.nf; ++f) {
-        const FrameDesc& df = f == 0u ? d : later[f - 1u];
-        // a pixel's record may pass from one lane to another between frames: the
-        // stores of the frame before are done before this one loads
-        if (f) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        }
-        tick_item<PS>(df, local, wave, sh);
-    }
+    if (d.stats) add_stats_wide(d.stats, slots, changed);
 }
 
-// The tick of table (head, descs), block by block; KIND: what the tick holds
-// (G = kTickAlone: no groups; kTickGroups: groups, none run as kGroup with k = 8;
-// kTickGroups8: some are; PS, + kTickPerSlot: frames of per-slot modes).  A group holds its pixels' whole records across
-// its frames, which takes more registers than the single-frame paths (at k = 8
-// far more), so each kind of tick runs the instantiation with only the paths
-// it needs, at the best occupancy they allow.
+// The tick of table (head, descs), block by block; KIND: what the tick holds (G =
+// kTickAlone: no groups; kTickStored: groups, all of them through the store; kTickGroups:
+// groups, some run as kGroup, none of these with k = 8; kTickGroups8: some with k = 8;
+// PS, + kTickPerSlot: frames of per-slot modes).  A group holds its pixels' whole
+// records across its frames, which takes more registers than the single-frame paths
+// (at k = 8 far more), and so does a per-slot frame's round, so each kind of tick
+// runs the instantiation with only the paths it needs, at the best occupancy they
+// allow without spilling registers.
 template <int KIND>
 __device__ __forceinline__ void tick_blocks(const TickHead& head, const FrameDesc* __restrict__ descs)
 {
@@ -1419,15 +1404,40 @@ __device__ __forceinline__ void tick_blocks(const TickHead& head, const FrameDes
     uint32_t local = item - d.first;
     if (d.rev) local = d.items - 1u - local;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if constexpr (G == kTickGroups || G == kTickGroups8) {
+        if (d.op == kGroup) {
+            tick_group_item<G>(d, descs, local, wave);
+            return;
+        }
+    }
     __shared__ TickShare<PS> share[kBlock / 64];
-    if (G != kTickAlone && d.nf > 1u) tick_group_item<G, PS>(d, descs, local, wave, share[wave]);
-    else tick_item<PS>(d, local, wave, share[wave]);
+    if constexpr (G == kTickAlone) {
+        tick_item<PS>(d, local, wave, threadIdx.x & 63u, share[wave]);
+    } else {
+#pragma nounroll
+        for (uint32_t f = 0; f < d.nf; ++f) {
+            // A pixel's record may pass from one lane of the wave to another between
+            // frames: no load may move above the stores of the frame before.  The wave's
+            // accesses then go through its compute unit's cache in that order.
+            if (f) {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            }
+            // opaque, so that what the paths of every slot count derive from it is not
+            // kept in registers over the loop
+            uint32_t lane = threadIdx.x & 63u;
+            asm volatile("" : "+v"(lane));
+            tick_item<PS>(f ? descs[d.more + f - 1u] : d, local, wave, lane, share[wave]);
+        }
+    }
 }
 
-// Waves per SIMD the kernels are compiled for.
+// Waves per SIMD the kernels are compiled for: the most that spill no register.
 constexpr int tick_waves(int kind)
 {
-    return kind % kTickPerSlot == kTickGroups8 ? 5 : kind == kTickAlone ? 8 : kind == kTickGroups ? 7 : 6;
+    constexpr int shared[] = {8, 8, 7, 5}, per_slot[] = {7, 7, 7, 5};
+    return kind < kTickPerSlot ? shared[kind] : per_slot[kind - kTickPerSlot];
 }
 
 // The table in device memory.
@@ -1581,7 +1591,7 @@ __device__ __forceinline__ void reproject_tile(const ReprojDesc& r, uint32_t ite
                 take = kn > Wj;
                 sj = take ? kn : Wj;
             } else {
-                take = decide_eq7(d, word, Wj, c.w, slot_delta<K>(t, c), sj);
+                take = decide_eq7(d, word, Wj, c.w, slot_delta<K>(t, c, lane), sj);
             }
         }
         const bool own = slot && (px.z & 1u) != 0u;
@@ -2004,8 +2014,8 @@ hipError_t launch_frame(const FrameDesc& d, int op, hipStream_t stream)
 }
 
 // One of a table of kernels, one per kind of tick.
-#define FWRS_TICK_KINDS(f) {f<0>, f<1>, f<2>, f<3>, f<4>, f<5>}
-static_assert(kTickKinds == 6, "a kernel per kind");
+#define FWRS_TICK_KINDS(f) {f<0>, f<1>, f<2>, f<3>, f<4>, f<5>, f<6>, f<7>}
+static_assert(kTickKinds == 8, "a kernel per kind");
 static void (*const kTickKernels[])(const TickHead*, const FrameDesc*) = FWRS_TICK_KINDS(tick_kernel);
 static void (*const kTickArgsKernels[])(TickArgs) = FWRS_TICK_KINDS(tick_args_kernel);
 #undef FWRS_TICK_KINDS
