@@ -1273,7 +1273,9 @@ __device__ __forceinline__ void frame_block(const FrameDesc& d, uint32_t block, 
 // of L1 between the first and the last.  resolve_pixel at 3840x2160: k = 8 213 us with 8
 // waves, 191 with 6, 188 with 4, 216 with 2; k = 4 107, 106, 103 and 110; k = 2 49.5, 50.7,
 // 52.5 and 69.  pixel_per_slot (T = 0), Eq. 7 and k = 4 at 3840x2160: 238.5 us with 8, 233.8
-// with 5, 229 with 3; with every colour changing 263, 268 and 294.
+// with 5, 229 with 3; with every colour changing 263, 268 and 294.  (Foveated frames,
+// which wait for samples of the frame first, are not held to 5: behind the mips, Eq. 7
+// and k = 4 at 3840x2160 312 us with 5, 302 with 8.)
 struct Waves {
     int least, most;
 };
@@ -1936,7 +1938,7 @@ __global__ __launch_bounds__(kBlock) void foveate_kernel(FoveateArgs a)
 }
 
 template <int K, bool PER_SLOT, int OP, int T = 1>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(frame_waves(K, OP, T).least, frame_waves(K, OP, T).most)))
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(frame_waves(K, OP, T).least, 8)))
 void foveated_kernel(FovDesc fd)
 {
     frame_block<K, OP, PER_SLOT, T, true>(fd.f, frame_item(blockIdx.x, gridDim.x, fd.f.t), &fd.s);
