@@ -13,8 +13,10 @@
 // A block of 256 threads covers one work item of 256 pixels, laid out as 1, 2
 // or 4 tiles of tile_x pixels by tile_y rows (the tile shape changes the access
 // pattern, never the results).  Decisions run with one lane per pixel, the work
-// on records with one lane per slot (stream_tiles).  The passes are bound by
-// their traffic to memory; there is no contraction anywhere, so no matrix cores.
+// on records with one lane per slot (stream_tiles, whole_tile, per_slot_tile), except
+// where one lane per pixel measured faster (resolve_pixel, pixel_per_slot,
+// pixel_group).  The passes are bound by their traffic to memory; there is no
+// contraction anywhere, so no matrix cores.
 //
 // Per pixel and frame (Sec. 4.1-4.2 of the paper):
 //   w    = Eq. 4 weight from the eccentricity to the gaze (level 0 -> 1)
@@ -44,8 +46,9 @@ namespace fwrs {
 // else); kCached: update + resolve of every pixel, where a pixel without a
 // replacement copies its resolve from the store's resolve plane (which holds it
 // unchanged since the pixel last changed) and a changed pixel recomputes it and
-// refreshes the plane; kCachedNt: kCached with non-temporal accesses to the plane; kFill: kFused that also writes every pixel's resolve into
-// the plane, making it valid for the kCached frames that follow.
+// refreshes the plane; kCachedNt: kCached with non-temporal accesses to the plane;
+// kFill: kFused that also writes every pixel's resolve into the plane, making it
+// valid for the kCached frames that follow.
 enum Op : int {
     kPush = kOpPush, kResolve = kOpResolve, kFused = kOpFused, kIncremental = kOpIncremental, kCached = kOpCached,
     kCachedNt = kOpCachedNt, kFill = kOpFill, kGroup = kOpGroup,
@@ -507,8 +510,9 @@ inline bool takes_two_tiles(const FrameDesc& d, int op)
 // is cheaper through L2 once the records are larger than the Infinity Cache (3840x2160,
 // k = 4, frame 80: 196 us against 214).  While they fit, the cache is better left to them:
 // kCachedNt 1920x1080, k = 4 44.7 -> 41.5, k = 8 1280x720 32.5 -> 30, behind the
-// mip generator at 1920x1080, k = 4 58.5 -> 50.  kIncremental (the output) up to 4 slots: 3840x2160, k = 2
-// 95 -> 79.6, 1280x720, k = 4 while filling 30.4 -> 28; at 8 145 -> 150 (2560x1440).
+// mip generator at 1920x1080, k = 4 58.5 -> 50.  kIncremental (the output) up to 4
+// slots: 3840x2160, k = 2 95 -> 79.6, 1280x720, k = 4 while filling 30.4 -> 28; at 8
+// 145 -> 150 (2560x1440).
 constexpr uint32_t scattered_nt(int k, int op) { return op == kCachedNt || (op == kIncremental && k >= 1 && k <= 4); }
 
 __device__ __forceinline__ void wave_lds_fence()
@@ -1307,7 +1311,7 @@ void frame_kernel(FrameDesc d)
 // the kernel keeps fewer values live (one more wave per SIMD).  A block finds
 // its item's leader by binary search over the leaders' first items.  An item of
 // a lone frame runs the single-frame per-pixel code for the frame's slot count
-// and op (kFused, kCached or kFill); an item of a group runs pixel_group (op
+// and op (kFused, kCached, kCachedNt or kFill); an item of a group runs pixel_group (op
 // kGroup), or else (run-time slot counts, per-slot modes) each of the group's
 // frames in turn through the store, every pixel in the same wave, so each
 // frame reads what the one before wrote.
