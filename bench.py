@@ -46,6 +46,8 @@ VALU_COUNTERS = os.path.join(ROOT, "profiles", "fused_valu_4k_counters.json")
 KERNEL_PLAIN = "void fwrs::frame_kernel<4, 3, false, 1>(fwrs::FrameDesc)"
 KERNEL_FILL = "void fwrs::frame_kernel<4, 9, false, 1>(fwrs::FrameDesc)"
 KERNEL_CACHED = "void fwrs::frame_kernel<4, 7, false, 1>(fwrs::FrameDesc)"
+KERNEL_INCREMENTAL = "void fwrs::frame_kernel<4, 5, false, 1>(fwrs::FrameDesc)"
+KERNEL_EQ7 = "void fwrs::frame_kernel<4, 3, true, 0>(fwrs::FrameDesc)"
 #: VALU issue peak of the MI355X for non-packed instructions, in lane-operations per second: one wave64
 #: instruction per compute unit and clock, 256 CUs x 64 lanes x 2.4 GHz (profiles/valu_issue_rate.md measures
 #: non-packed fp32 fma / mul / add at 0.92-0.98 of it; the published 157.3 TFLOP/s fp32 vector rate counts packed
@@ -742,7 +744,7 @@ def main() -> int:
                        "roofline": {"bound": "hbm", "achieved": i_ach, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                                     "frac": i_ach / HBM_PEAK_GBPS,
                                     "traffic": traffic_from_counters(
-                                        "void fwrs::frame_kernel<4, 5, false, 2>(fwrs::FrameDesc)", spec.pixels,
+                                        KERNEL_INCREMENTAL, spec.pixels,
                                         {"steps": K, "frames_per_step": fps, "frames": n_frames}, INC_COUNTERS),
                                     "kernel_ms_avg": i_kern,
                                     "bytes_per_pixel_update": i_B, "slot_takes_per_pixel_update": i_rbar,
@@ -766,8 +768,7 @@ def main() -> int:
         f_B = bytes_per_update_eq7(spec.k, f_rbar)
         f_kern = float(f_per.mean())
         f_ach = spec.pixels * f_B / (f_kern / 1e3) / 1e9
-        e7_kernel = "void fwrs::frame_kernel<4, 3, true, 1>(fwrs::FrameDesc)"
-        vpp = valu_per_pixel(e7_kernel)
+        vpp = valu_per_pixel(KERNEL_EQ7)
         alu = None
         if vpp is not None:
             a_t = spec.pixels * vpp / (f_kern / 1e3) / 1e12
@@ -776,7 +777,7 @@ def main() -> int:
                    "wave_insts_per_cu_clock": a_t * 1e12 / 64.0 / 256.0 / 2.4e9,
                    "note": "all VALU instructions (SQ_INSTS_VALU) against one non-packed wave64 instruction per CU "
                            "and clock",
-                   "kernel": "fwrs::frame_kernel<4, 3, true, 1> (Eq. 7)"}
+                   "kernel": KERNEL_EQ7[5:].split("(")[0] + " (Eq. 7)"}
         eq7 = {"entry": "fwrs_push_frame_resolve (FWRS_BIAS_FULL)", "frames": n_frames,
                "ms_per_frame": f_ms / n_frames,
                "value": spec.pixels * n_frames / (f_ms / 1e3) / 1e9, "unit": "Gpixel-updates/s",
@@ -785,7 +786,7 @@ def main() -> int:
                "roofline": {"bound": "hbm", "achieved": f_ach, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                             "frac": f_ach / HBM_PEAK_GBPS,
                             "traffic": traffic_from_counters(
-                                e7_kernel, spec.pixels, {"steps": K, "frames_per_step": fps, "frames": n_frames},
+                                KERNEL_EQ7, spec.pixels, {"steps": K, "frames_per_step": fps, "frames": n_frames},
                                 EQ7_COUNTERS),
                             "kernel_ms_avg": f_kern, "bytes_per_pixel_update": f_B,
                             "slot_takes_per_pixel_update": f_rbar},
