@@ -1961,20 +1961,13 @@ template <int OP, int T>
 static hipError_t launch_shared(const FrameDesc& d, hipStream_t stream)
 {
     const dim3 grid((d.items + (uint32_t)T - 1u) / (uint32_t)T), block(kBlock);
-    if constexpr (T == 2) {
-        switch (d.k) {
-            case 1: hipLaunchKernelGGL((frame_kernel<1, OP, false, T>), grid, block, 0, stream, d); break;
-            case 2: hipLaunchKernelGGL((frame_kernel<2, OP, false, T>), grid, block, 0, stream, d); break;
-            case 4: hipLaunchKernelGGL((frame_kernel<4, OP, false, T>), grid, block, 0, stream, d); break;
-            default: hipLaunchKernelGGL((frame_kernel<0, OP, false, T>), grid, block, 0, stream, d); break;
-        }
-        return hipGetLastError();
-    }
     switch (d.k) {
         case 1: hipLaunchKernelGGL((frame_kernel<1, OP, false, T>), grid, block, 0, stream, d); break;
         case 2: hipLaunchKernelGGL((frame_kernel<2, OP, false, T>), grid, block, 0, stream, d); break;
         case 4: hipLaunchKernelGGL((frame_kernel<4, OP, false, T>), grid, block, 0, stream, d); break;
-        case 8: hipLaunchKernelGGL((frame_kernel<8, OP, false, T>), grid, block, 0, stream, d); break;
+        case 8:                                         // two tiles: up to 4 slots (takes_two_tiles)
+            if constexpr (T == 1) hipLaunchKernelGGL((frame_kernel<8, OP, false, T>), grid, block, 0, stream, d);
+            break;
         default: hipLaunchKernelGGL((frame_kernel<0, OP, false, T>), grid, block, 0, stream, d); break;
     }
     return hipGetLastError();

@@ -3,6 +3,7 @@ memory -- a kernel that spills registers pays for it on every frame -- and the b
 occupancy they are compiled for (CPU only)."""
 from __future__ import annotations
 
+import re
 import struct
 
 import msgpack
@@ -65,3 +66,13 @@ def test_batched_kernels_keep_their_occupancy(kernels):
         for name in (f"_ZN4fwrs11tick_kernelILi{kind}E", f"_ZN4fwrs16tick_args_kernelILi{kind}E"):
             k = next(v for n, v in kernels.items() if n.startswith(name))
             assert 512 // ((k[".vgpr_count"] + 7) // 8 * 8) >= waves, (name, k[".vgpr_count"])
+
+
+def test_the_frame_kernels_are_those_that_the_rules_launch(kernels):
+    """frame_kernel<slots, op, per-slot mode, tiles>: every instantiation is one that some frame takes."""
+    launched = {(k, op, 0, 1) for k in (0, 1, 2, 4, 8) for op in (1, 2, 3, 5, 7, 8, 9)}
+    launched |= {(k, op, 0, 2) for k in (0, 1, 2, 4) for op in (1, 5)}
+    launched |= {(k, op, 1, t) for k, t in ((0, 1), (1, 1), (2, 1), (3, 0), (4, 0), (5, 0), (8, 0)) for op in (1, 3, 5)}
+    built = {tuple(map(int, m.groups())) for m in
+             (re.match(r"_ZN4fwrs12frame_kernelILi(\d+)ELi(\d+)ELb([01])ELi(\d+)E", n) for n in kernels) if m}
+    assert built == launched
